@@ -327,13 +327,12 @@ __device__ __forceinline__ void wave_lds_fence() {
 // Entry for slot: f | (slot - cum) << 12 | sym << 24.
 // Returns false (uniformly) if the stored table is not a valid ANS table.
 // ---------------------------------------------------------------------------
-__device__ void fill_lut(const uint32_t f[4], uint32_t *lut, uint16_t *cum_s, uint16_t *f_s);
+__device__ void fill_lut(const uint32_t f[4], uint32_t *lut);
 // The caller loaded the section's start: `byte` is byte 256 + lane / 2 of
 // the section (the presence bits), `fa` its bytes 288 + 8 lane .. + 7 (the
 // u16 frequencies of ranks 4 lane .. 4 lane + 3; zero past the section's
 // end).
-__device__ bool build_lut_pre(uint32_t byte, uint2 fa, uint64_t sec_len, uint32_t *lut, uint16_t *cum_s,
-                              uint16_t *f_s, uint32_t &k_out) {
+__device__ bool build_lut_pre(uint32_t byte, uint2 fa, uint64_t sec_len, uint32_t *lut, uint32_t &k_out) {
   const uint32_t lane = lane_id();
   if (sec_len < kSectionFixed) return false;
   const uint32_t nib = (byte >> (4 * (lane & 1))) & 0xFu;
@@ -358,55 +357,67 @@ __device__ bool build_lut_pre(uint32_t byte, uint2 fa, uint64_t sec_len, uint32_
   const uint32_t bad = (nib & 1 && f[0] == 0) | (nib & 2 && f[1] == 0) | (nib & 4 && f[2] == 0) |
                        (nib & 8 && f[3] == 0);
   if (!(ok0 && !__any(bad) && wave_sum(total) == kM)) return false;
-  fill_lut(f, lut, cum_s, f_s);
+  fill_lut(f, lut);
   k_out = k;
   return true;
 }
 
 // The lookup table from this lane's frequencies f[4] of symbols 4 lane ..
-// 4 lane + 3 (summing to M over the wave).
-__device__ void fill_lut(const uint32_t f[4], uint32_t *lut, uint16_t *cum_s, uint16_t *f_s) {
+// 4 lane + 3 (summing to M over the wave).  Every present symbol's first
+// slot gets its entry (f | sym << 24, remainder 0), the other slots 0; a lane
+// then fills slots 32 lane .. 32 lane + 31, each slot without an entry
+// taking the one before it with the remainder one higher.  The entry its
+// first slot continues is that of the largest first slot below it (a wave
+// scan).  (A search of the slot's symbol per lane and a walk over the
+// cumulative frequencies took 32 dependent LDS reads: 5300 cycles, 1900 this
+// way.)
+__device__ void fill_lut(const uint32_t f[4], uint32_t *lut) {
   const uint32_t lane = lane_id();
+  uint4 *mine = (uint4 *)(lut + 32 * lane);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) mine[j] = make_uint4(0u, 0u, 0u, 0u);
   uint32_t c = wave_excl_scan(f[0] + f[1] + f[2] + f[3]);
+  wave_lds_fence();
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
-    cum_s[4 * lane + q] = (uint16_t)c;
-    f_s[4 * lane + q] = (uint16_t)f[q];
+    if (f[q]) lut[c] = f[q] | (4 * lane + q) << 24;
     c += f[q];
   }
   wave_lds_fence();
-  // lane fills slots 32 lane .. 32 lane + 31: find the owner of the first one
-  uint32_t slot = 32 * lane;
-  uint32_t lo = 0, hi = 255;  // largest s with cum[s] <= slot
-  while (lo < hi) {
-    uint32_t mid = (lo + hi + 1) >> 1;
-    if (cum_s[mid] <= slot)
-      lo = mid;
-    else
-      hi = mid - 1;
+  uint32_t w[32];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const uint4 v = mine[j];
+    w[4 * j] = v.x, w[4 * j + 1] = v.y, w[4 * j + 2] = v.z, w[4 * j + 3] = v.w;
   }
-  uint32_t s = lo;
-  uint32_t c0 = cum_s[s], fs = f_s[s];
-  for (uint32_t q = 0; q < 32; ++q, ++slot) {
-    while (slot >= c0 + fs) {
-      ++s;
-      c0 = cum_s[s];
-      fs = f_s[s];
-    }
-    lut[slot] = fs | ((slot - c0) << 12) | (s << 24);
+  // 1 + the last slot of this lane that starts a symbol, 0 if none
+  uint32_t lastp = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < 32; ++j) lastp = w[j] ? 32 * lane + j + 1 : lastp;
+  const uint32_t prev = wave_excl_max(lastp);
+  // (slot 0 starts a symbol: only lane 0 has none before it, and needs none)
+  const uint32_t p = prev ? prev - 1 : 0u;
+  uint32_t e = lut[p] + ((32 * lane - p - 1) << 12);
+  wave_lds_fence();  // read before the entries change
+#pragma unroll
+  for (uint32_t j = 0; j < 32; ++j) {
+    e = w[j] ? w[j] : e + (1u << 12);
+    w[j] = e;
   }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) mine[j] = make_uint4(w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]);
   wave_lds_fence();
 }
 
 // Lookup table of a stream-wide table (u16 f[256] in memory): every symbol
 // has f >= 1 and the sum is M, else false (uniformly).
-__device__ bool build_lut_shared(const uint16_t *table, uint32_t *lut, uint16_t *cum_s, uint16_t *f_s) {
+__device__ bool build_lut_shared(const uint16_t *table, uint32_t *lut) {
   const uint32_t lane = lane_id();
   const uint2 v = *(const uint2 *)(table + 4 * lane);
   const uint32_t f[4] = {v.x & 0xFFFFu, v.x >> 16, v.y & 0xFFFFu, v.y >> 16};
   const bool bad = f[0] == 0 || f[1] == 0 || f[2] == 0 || f[3] == 0;
   if (__any(bad) || wave_sum(f[0] + f[1] + f[2] + f[3]) != kM) return false;
-  fill_lut(f, lut, cum_s, f_s);
+  fill_lut(f, lut);
   return true;
 }
 
@@ -1676,93 +1687,235 @@ __global__ void __launch_bounds__(64) reduce_kernel(EncodeArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Table decoding: the decode sub-step shared by decode_kernel and the fused
-// reduce's decoding waves, and the fused reduce's word ring.
+// Table decoding, shared by decode_kernel and the fused reduce's decoding
+// waves.
 //
-// In the fused reduce the words of a coded block are staged through a 4 KB
-// LDS ring in 1 KB chunks read with one 16-byte load per lane: a chunk is
-// loaded as soon as the ring has room and written to LDS only when the
-// decoder is about to need it, so the serial decode chain only ever waits on
-// LDS.  The raw plane of the next round is loaded one round ahead.
-// decode_kernel's own ring (2 KB, more waves per CU) is described with it.
+// A decode sub-step is bound by its dependent LDS reads: a read takes ~65
+// cycles, a vector instruction 8 (and a lone wave issues one instruction in
+// ~6), and with the table read waiting for the renormalisation word (the
+// next slot is the word's low 11 bits) a block's chain took two reads, ~220
+// cycles a sub-step on an otherwise idle SIMD.  The words are known ahead,
+// though: when a chunk of them enters the ring, each word's table entry is
+// looked up once (64 words at a time, a sixth of a lookup per sub-step for
+// bf16 weights) and the ring holds what the entry and the word make
+// together.  The renormalising lanes then read their next entry in place of
+// their word, the other lanes read the table, and the two reads overlap: one
+// LDS latency per sub-step, in whose shadow the previous round's elements
+// are merged and stored.
+//
+// The coder state x is carried as e, t, r with x' = f t + r its next value
+// before renormalisation: of a state with table entry (f, rem, sym),
+// e = f | sym << 24 (bits 12..23 clear, so a 24-bit product takes it as f),
+// t = x >> 11 and r = rem; of a state just renormalised from x by word w,
+// t = x << 5 and r = rem + f (w >> 11).  Ring entry of word w (8 bytes):
+// e and r of its slot w & 2047.
+// Measured (interleaved A/B against the two-read chain with a ring of plain
+// words): 171 cycles a sub-step on a lone wave, 256 KiB of bf16 53.9 -> 40.3
+// us, 214 MB of fp32 119 -> 95 us, the 1 GiB weight buffer 404 -> 391 us (3
+// waves a SIMD instead of 4: it is held by memory, 4.57 TB/s).  A lone wave
+// issues an instruction in ~5 cycles whatever it depends on, so what is left
+// of the chain is its ~26 instructions.
+//
+// 512 entries and a mirror of the first 64 (one step's reads never wrap):
+// with the 8 KB table 12.5 KB of LDS per wave.  Words enter in chunks of 256
+// (8 bytes a lane) when fewer than 256 are left at the start of a half round
+// (4 sub-steps of at most 64 words), from registers that hold the next
+// chunks.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kRingBytes = 4096;
-constexpr uint32_t kRingMirror = 128;  // ring[0, 128) repeated past the end: one step's reads never wrap
-constexpr uint32_t kChunkBytes = 1024;
+constexpr uint32_t kRingWords = 512, kRingChunk = 256, kRingMirror = 64;
+constexpr uint32_t kRingBytes = 8 * (kRingWords + kRingMirror);
+
+// Words in their ring (all wave-uniform but the chunks in registers).  Once
+// a round the chunk asked for a round earlier lands and a load follows: of
+// the next chunk if fewer than two are on their way or waiting, else of the
+// newest one again, so that every path through a round issues the same
+// memory operations and the compiler's waits (one in-order counter for loads
+// and stores) stay exact.  (One chunk a round is the mean rate at which a
+// block is not worth coding; a burst that drains the waiting chunks loads
+// one on the spot.)
+struct WordRing {
+  const uint8_t *sec;  // the block's section
+  uint32_t last;       // section offset of its last 8 bytes
+  uint32_t front;      // words in the ring so far, counted from the first chunk's start
+  uint32_t off;        // section offset of the newest chunk asked for
+  uint32_t q;          // 8 x the words consumed
+  uint32_t n;          // chunks landed and not stored yet (s0, s1), at most 2
+  bool u;              // f is a chunk that has not landed yet
+  uint2 s0, s1, f;     // this lane's 4 words of a chunk
+};
+
+typedef __attribute__((address_space(3))) uint8_t lds8_t;
+typedef __attribute__((address_space(3))) uint32_t lds32_t;
+constexpr uint32_t kEntryMask = 0xFF000FFFu;  // f and symbol of a table entry
+
+// The coder states of a wave (64 lanes), see above.
+struct DecState {
+  uint32_t e, t, r;
+};
+__device__ __forceinline__ DecState dec_state(uint32_t x, const uint32_t *lut) {
+  const uint32_t el = lut[x & (kM - 1)];
+  return DecState{el & kEntryMask, x >> kProbBits, (el >> 12) & 0x7FFu};
+}
+// back at the initial state 2^15 (no renormalisation ends there)
+__device__ __forceinline__ bool dec_at_start(const DecState &d, const uint32_t *lut) {
+  const DecState s = dec_state(kStateLo, lut);
+  return d.e == s.e && d.t == s.t && d.r == s.r;
+}
 
 // One decode sub-step of every lane (inverse of the coding function, then
-// 16-bit renormalisation).  Returns the lane's table entry (its symbol in the
-// top byte; 0 for a lane without an element).  Branch-free: every lane reads
-// the ring at its would-be word position rb + 2 * rank (rb: ring offset of
-// the next unread word, uniform); lanes that need no word keep their state.
-// Positions past the section's words stay inside the ring and are caught
-// once per block by p <= w_avail.
-template <bool FULL, uint32_t RB = kRingBytes, bool MIRROR = true>
-__device__ __forceinline__ uint32_t decode_step_ring(uint32_t &x, bool valid, const uint32_t *lut,
-                                                     const uint8_t *ring, uint32_t &rb, uint32_t &p) {
-  uint32_t e = 0;
-  if (FULL || valid) {
-    e = lut[x & (kM - 1)];
-    x = __umul24(e & 0xFFFu, x >> kProbBits) + ((e >> 12) & 0x7FFu);
-  }
+// 16-bit renormalisation), `fill` being other work for the shadow of its
+// LDS reads.  Returns the entry used (its symbol in the top byte; 0 for a
+// lane without an element).  Branch-free: every lane reads the table at its
+// new state's slot and the ring at its would-be word; positions past the
+// section's words stay inside the ring and are caught once per block.
+template <bool FULL, typename F>
+__device__ __forceinline__ uint32_t decode_step(DecState &d, bool valid, const uint32_t *lut, const uint8_t *ring,
+                                                uint32_t &q, F fill) {
+  typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+  const uint32_t used = d.e;
+  const uint32_t x = __umul24(d.e, d.t) + d.r;
+  // (volatile: unconditional reads, this one first, with no exec-mask branch around them)
+  const uint32_t el = ((const volatile lds32_t *)lut)[x & (kM - 1)];
   const bool need = (FULL || valid) && x < kStateLo;
   const uint64_t m = __ballot(need);
   const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-  uint32_t w = *(const uint16_t *)(ring + (MIRROR ? rb + 2 * rank : (rb + 2 * rank) & (RB - 1)));
-  asm volatile("" : "+v"(w));  // keep the read unconditional: no exec-mask branch around it
-  x = need ? ((x << 16) | w) : x;
-  const uint32_t c = (uint32_t)__popcll(m);
-  p += c;
-  rb = (rb + 2 * c) & (RB - 1);
-  // the ring offset stays a scalar of its own: the compiler would rebuild it
-  // from p with one more vector add per sub-step
-  rb = __builtin_amdgcn_readfirstlane(rb);
-  return e;
+  const uint32_t rb = q & (8 * kRingWords - 1);
+  const v2u v = *(const volatile __attribute__((address_space(3))) v2u *)((const lds8_t *)ring + (rb + 8 * rank));
+  __builtin_amdgcn_sched_barrier(0);
+  // (the compiler would keep a sum of the counts besides)
+  q = uniform(q);
+  asm("s_lshl3_add_u32 %0, %1, %0" : "+s"(q) : "s"((uint32_t)__popcll(m)) : "scc");
+  const uint32_t t = need ? x << 5 : x >> kProbBits;
+  fill();
+  const uint32_t ef = el & kEntryMask, er = (el >> 12) & 0x7FFu;
+  __builtin_amdgcn_sched_barrier(0);
+  const uint32_t e = need ? v.x : ef;
+  const uint32_t r = need ? v.y : er;
+  d.t = (FULL || valid) ? t : d.t;
+  d.e = (FULL || valid) ? e : d.e;
+  d.r = (FULL || valid) ? r : d.r;
+  return (FULL || valid) ? used : 0u;
 }
 
-// 16 bytes of section words into the ring at pos and, for the first 128
-// bytes, into the mirror (the other lanes store to pos twice: no branch)
-__device__ __forceinline__ void ring_put(uint8_t *ring, uint32_t pos, uint4 v) {
-  *(uint4 *)(ring + pos) = v;
-  *(uint4 *)(ring + (pos < kRingMirror ? kRingBytes + pos : pos)) = v;
+// A chunk's 4 words of this lane into the ring at word `slot` (0 or 256).
+__device__ __forceinline__ uint2 ring_entry(const uint32_t *lut, uint32_t w) {
+  const uint32_t e = lut[w & (kM - 1)];
+  return make_uint2(e & kEntryMask, __umul24(e & 0xFFFu, w >> kProbBits) + ((e >> 12) & 0x7FFu));
 }
-
-// Eight decoded elements of one lane from their table entries (symbols in
-// the top bytes) and raw bytes: the inverse of the byte-plane split.
-template <int DT>
-__device__ inline void merge_entries(const uint32_t e[8], const uint32_t raw[6],
-                                     uint32_t w[4 * (dt_bytes<DT>() / 2)]) {
-  if constexpr (DT <= 1) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      // [raw, sym, raw, sym] of elements 2j, 2j + 1, then rotate each half back
-      const uint32_t t = __builtin_amdgcn_perm(e[2 * j], raw[j >> 1], (j & 1) ? 0x07030702u : 0x07010700u);
-      w[j] = rotr16x2(__builtin_amdgcn_perm(e[2 * j + 1], t, 0x07020100u));
-    }
-  } else {
-    uint32_t sym[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t lo = __builtin_amdgcn_perm(e[4 * h + 1], e[4 * h], 0x07070703u);
-      const uint32_t hi = __builtin_amdgcn_perm(e[4 * h + 3], e[4 * h + 2], 0x07030303u);
-      sym[h] = __builtin_amdgcn_perm(hi, lo, 0x07060100u);
-    }
-    merge_group<DT>(sym, raw, w);
+__device__ __forceinline__ void ring_put(uint8_t *ring, const uint32_t *lut, uint32_t slot, uint2 v) {
+  const uint32_t lane = lane_id();
+  const uint2 e0 = ring_entry(lut, v.x & 0xFFFFu), e1 = ring_entry(lut, v.x >> 16);
+  const uint2 e2 = ring_entry(lut, v.y & 0xFFFFu), e3 = ring_entry(lut, v.y >> 16);
+  const uint4 a = make_uint4(e0.x, e0.y, e1.x, e1.y), b = make_uint4(e2.x, e2.y, e3.x, e3.y);
+  uint4 *d = (uint4 *)(ring + 8 * slot + 32 * lane);
+  d[0] = a;
+  d[1] = b;
+  if (slot == 0 && lane < kRingMirror / 4) {
+    uint4 *dm = (uint4 *)(ring + 8 * kRingWords + 32 * lane);
+    dm[0] = a;
+    dm[1] = b;
   }
 }
 
+// 8 bytes of this lane's part of the chunk at section offset `o` (clamped to
+// the section: words past its end are never consumed)
+__device__ __forceinline__ uint2 ring_load(const uint8_t *sec, uint32_t o, uint32_t last) {
+  const uint32_t p = o + 8 * lane_id();
+  return *(const uint2 *)(sec + (p < last ? p : last));
+}
 
-// Ring bookkeeping of one coded block (all members wave-uniform).
-struct Ring {
-  uint32_t written;  // section bytes [written - 4096, written) are in the ring
-  uint32_t len;      // section length (a multiple of 16)
-  uint4 pv;          // this lane's 16 bytes of the chunk at `written`, loaded a round ahead
-};
+// Before each half round: at least 256 words in the ring.
+__device__ __forceinline__ void ring_fill(WordRing &rg, uint8_t *ring, const uint32_t *lut) {
+  if (__builtin_expect(8 * (rg.front - kRingChunk) < rg.q, 0)) {
+    if (__builtin_expect(rg.n == 0, 0)) {  // a burst: the next chunk at once
+      rg.off += rg.u ? 0 : 2 * kRingChunk;
+      rg.s0 = ring_load(rg.sec, rg.off, rg.last);
+      rg.u = false;
+      rg.n = 1;
+    }
+    ring_put(ring, lut, rg.front & (kRingWords - 1), rg.s0);
+    asm volatile("" ::: "memory");  // the ring stores stay before the half round's ring reads
+    rg.s0 = rg.s1;
+    rg.front += kRingChunk;
+    --rg.n;
+  }
+}
+// Once a round, before its first ring_fill.
+__device__ __forceinline__ void ring_land(WordRing &rg) {
+  if (__builtin_expect(rg.u, 0)) {
+    asm volatile("" : "+v"(rg.f.x), "+v"(rg.f.y));  // (a branch: selects would wait for the load every time)
+    if (rg.n == 0) rg.s0 = rg.f;
+    else rg.s1 = rg.f;
+    ++rg.n;
+  }
+  rg.u = rg.n < 2;
+  rg.off += rg.u ? 2 * kRingChunk : 0;
+  rg.f = ring_load(rg.sec, rg.off, rg.last);
+}
 
-// 16 bytes of this lane's part of the chunk at section offset o (clamped to
-// the section: a chunk past the end is never decoded from)
-__device__ __forceinline__ uint4 ring_fetch(const uint8_t *sec, uint32_t o, uint32_t len) {
-  return *(const uint4 *)(sec + (o + 16 <= len ? o : len - 16));
+// A coded block's ring once its table is in LDS: its words start at section
+// offset wb, and a, b hold bytes 32 lane .. 32 lane + 31 of the 2048 section
+// bytes from p0 (p0 <= wb <= p0 + 512; zero past the section's end).  The
+// ring starts with the two chunks from the word start's 16-byte unit on, the
+// third waits in registers.
+__device__ __forceinline__ void ring_open(WordRing &rg, uint8_t *ring, const uint32_t *lut, const uint8_t *sec,
+                                          uint32_t len, uint32_t wb, uint32_t p0, uint4 a, uint4 b) {
+  const uint32_t lane = lane_id();
+  const uint32_t base = wb & ~15u;
+  rg.sec = sec;
+  rg.last = len - 8;
+  // the raw bytes pass through the ring's place to reach their lanes
+  wave_lds_fence();
+  uint4 *d = (uint4 *)(ring + 32 * lane);
+  d[0] = a;
+  d[1] = b;
+  wave_lds_fence();
+  const uint8_t *r = ring + (base - p0) + 8 * lane;
+  const uint2 c0 = *(const uint2 *)r, c1 = *(const uint2 *)(r + 2 * kRingChunk);
+  rg.s0 = *(const uint2 *)(r + 4 * kRingChunk);
+  rg.s1 = rg.f = rg.s0;
+  wave_lds_fence();
+  ring_put(ring, lut, 0, c0);
+  ring_put(ring, lut, kRingChunk, c1);
+  rg.front = 2 * kRingChunk;
+  rg.off = base + 4 * kRingChunk;
+  rg.n = 1;
+  rg.u = false;
+  rg.q = 4 * (wb - base);
+  wave_lds_fence();
+}
+
+// Words consumed by the block (its first word was at section offset wb).
+__device__ __forceinline__ uint32_t ring_used(const WordRing &rg, uint32_t wb) { return (rg.q >> 3) - (wb & 15u) / 2; }
+
+// Quarter j (elements 2j, 2j + 1) of eight decoded elements of one lane from
+// their table entries (symbols in the top bytes) and raw bytes: the inverse
+// of the byte-plane split.  Types other than bf16 and fp16 merge in halves
+// (j = 1 and 3).
+template <int DT>
+__device__ __forceinline__ void merge_quarter(int j, const uint32_t e[8], const uint32_t raw[6],
+                                              uint32_t w[4 * (dt_bytes<DT>() / 2)]) {
+  if constexpr (DT <= 1) {
+    // [raw, sym, raw, sym] of elements 2j, 2j + 1, then rotate each half back
+    const uint32_t t = __builtin_amdgcn_perm(e[2 * j], raw[j >> 1], (j & 1) ? 0x07030702u : 0x07010700u);
+    w[j] = rotr16x2(__builtin_amdgcn_perm(e[2 * j + 1], t, 0x07020100u));
+  } else if (j & 1) {
+    const int h = j >> 1;
+    const uint32_t lo = __builtin_amdgcn_perm(e[4 * h + 1], e[4 * h], 0x07070703u);
+    const uint32_t hi = __builtin_amdgcn_perm(e[4 * h + 3], e[4 * h + 2], 0x07030303u);
+    const uint32_t sym = __builtin_amdgcn_perm(hi, lo, 0x07060100u);
+    if constexpr (DT >= 3) {
+      merge8x2_half(sym, raw[h], w + 2 * h);
+    } else {
+      merge32_half(sym, raw + 3 * h, w + 4 * h);
+    }
+  }
+}
+template <int DT>
+__device__ inline void merge_entries(const uint32_t e[8], const uint32_t raw[6],
+                                     uint32_t w[4 * (dt_bytes<DT>() / 2)]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) merge_quarter<DT>(j, e, raw, w);
 }
 
 // A stream header's eight words (loaded by the caller, ahead of their use).
@@ -1770,6 +1923,9 @@ struct Hdr {
   uint4 lo, hi;
 };
 __device__ inline Hdr load_hdr(const uint8_t *s) { return Hdr{((const uint4 *)s)[0], ((const uint4 *)s)[1]}; }
+// the same words as scalars (every lane loaded the same)
+__device__ inline uint4 uniform4(uint4 v) { return make_uint4(uniform(v.x), uniform(v.y), uniform(v.z), uniform(v.w)); }
+__device__ inline Hdr uniform_hdr(const Hdr &h) { return Hdr{uniform4(h.lo), uniform4(h.hi)}; }
 
 // Modes of a decoding wave's input block in the fused reduce.
 enum : uint32_t { kBad = 0, kStored = 1, kCoded = 2 };
@@ -1779,25 +1935,26 @@ enum : uint32_t { kBad = 0, kStored = 1, kCoded = 2 };
 // block's directory entries, and for a coded block builds the lookup table
 // and fills the ring.  The loads come in two rounds: the header with the
 // directory entries, then the start of the section -- states, presence
-// bits, frequencies and the 4096 bytes from the end of the fixed part,
-// which hold the first two ring chunks and the first pending one (the
-// words begin at most 512 bytes in) -- instead of five dependent ones.
+// bits, frequencies and the 2048 bytes from the end of the fixed part, which
+// hold the first three chunks of words (they begin at most 512 bytes in) --
+// instead of five dependent ones.
 // Returns kBad, kStored or kCoded; sets sec, raw_plane, the states x, the
 // word start wb, the words available and the ring.
 template <int DT>
 __device__ uint32_t open_input_block(const uint8_t *s, uint64_t in_bytes, uint64_t n, uint32_t be, uint32_t b,
                                      uint32_t n_b, uint32_t *lut, uint8_t *ring, const uint8_t *&sec,
                                      const uint8_t *&raw_plane, uint32_t &x, uint32_t &wb, uint32_t &w_avail,
-                                     Ring &rg) {
+                                     WordRing &rg) {
   constexpr int E = (DT == 2) ? 4 : 2;
   const uint32_t lane = lane_id();
   const Geom g = make_geom(n, be, E);
   if (in_bytes < kHeaderBytes) return kBad;
   // round 1: header and directory entries (inside the stream's bytes)
-  const Hdr h = load_hdr(s);
+  const Hdr hv = load_hdr(s);
   const uint64_t de = kHeaderBytes + 4ull * (b + 1);
-  const uint32_t d = de <= in_bytes ? ld32(s + de - 4) : 0u;
-  const uint32_t dp = (b > 0 && de <= in_bytes) ? ld32(s + de - 8) : 0u;
+  const uint32_t d = uniform(de <= in_bytes ? ld32(s + de - 4) : 0u);
+  const uint32_t dp = uniform((b > 0 && de <= in_bytes) ? ld32(s + de - 8) : 0u);
+  const Hdr h = uniform_hdr(hv);
   const uint64_t start = b ? 16ull * (dp & ~kStoredBit) : 0;
   const uint64_t end = 16ull * (d & ~kStoredBit);
   const bool stored = d >> 31;
@@ -1806,8 +1963,7 @@ __device__ uint32_t open_input_block(const uint8_t *s, uint64_t in_bytes, uint64
   // loads of a section of 16-byte units are whole inside it or skipped)
   uint32_t pbyte = 0;
   uint2 pfa = make_uint2(0u, 0u);
-  uint4 pre[4] = {make_uint4(0u, 0u, 0u, 0u), make_uint4(0u, 0u, 0u, 0u), make_uint4(0u, 0u, 0u, 0u),
-                  make_uint4(0u, 0u, 0u, 0u)};
+  uint4 pre0 = make_uint4(0u, 0u, 0u, 0u), pre1 = pre0;
   const uint8_t *sc = s + g.coded_off + start;
   uint32_t xs = kStateLo;
   x = kStateLo;
@@ -1815,11 +1971,9 @@ __device__ uint32_t open_input_block(const uint8_t *s, uint64_t in_bytes, uint64
     xs = ((const uint32_t *)sc)[lane];
     pbyte = sc[256 + (lane >> 1)];
     if (kSectionFixed + 8 * lane + 8 <= len) pfa = *(const uint2 *)(sc + kSectionFixed + 8 * lane);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t o = kSectionFixed + 1024 * j + 16 * lane;
-      if (o + 16 <= len) pre[j] = *(const uint4 *)(sc + o);
-    }
+    const uint32_t o0 = kSectionFixed + 32 * lane;
+    if (o0 + 16 <= len) pre0 = *(const uint4 *)(sc + o0);
+    if (o0 + 32 <= len) pre1 = *(const uint4 *)(sc + o0 + 16);
   }
   const uint64_t total = (uint64_t)h.hi.z | (uint64_t)h.hi.w << 32;
   const bool ok = h.lo.x == kMagic && h.lo.y == (kVersion | ((uint32_t)DT << 8) | (kProbBits << 16)) &&
@@ -1831,68 +1985,13 @@ __device__ uint32_t open_input_block(const uint8_t *s, uint64_t in_bytes, uint64
   raw_plane = s + g.raw_off;
   if (stored) return len >= n_b ? kStored : kBad;
   uint32_t k = 0;
-  if (!build_lut_pre(pbyte, pfa, len, lut, (uint16_t *)ring, (uint16_t *)ring + 256, k)) return kBad;
+  if (!build_lut_pre(pbyte, pfa, len, lut, k)) return kBad;
   k = uniform(k);
   x = xs;
   wb = kSectionFixed + 2 * k;
   w_avail = (len - wb) / 2;
-  rg.len = len;
-  // section bytes [288, 288 + 4096) fill the ring (the table build's
-  // scratch until now): it then holds the two chunks from the word start's
-  // 16-byte unit on, and the third is the first pending one
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const uint32_t o = kSectionFixed + 1024 * j + 16 * lane;
-    ring_put(ring, o & (kRingBytes - 1), pre[j]);
-  }
-  wave_lds_fence();
-  rg.written = (wb & ~15u) + 2 * kChunkBytes;
-  rg.pv = *(const uint4 *)(ring + ((rg.written + 16 * lane) & (kRingBytes - 1)));
+  ring_open(rg, ring, lut, sc, len, wb, kSectionFixed, pre0, pre1);
   return kCoded;
-}
-
-// Before a round: make sure the next 1 KB of words (from section offset cur)
-// is in LDS, then load the following chunk for the next round.  Every round
-// stores the loaded chunk at its ring position and loads the chunk at
-// `written` again, also when neither has moved (a repeat store of the same
-// bytes; a cache hit): every path through a round then issues the same
-// memory operations, so no wait for them lands inside the decode chain.
-// The store never overwrites unread words: written < cur + 2048 always.
-__device__ __forceinline__ void ring_maintain(Ring &rg, uint8_t *ring, const uint8_t *sec, uint32_t cur) {
-  const uint32_t lane = lane_id();
-  ring_put(ring, (rg.written + 16 * lane) & (kRingBytes - 1), rg.pv);
-  asm volatile("" ::: "memory");  // the ring stores stay before the round's ring reads
-  rg.written += rg.written < cur + kChunkBytes ? kChunkBytes : 0;
-  rg.pv = ring_fetch(sec, rg.written + 16 * lane, rg.len);
-}
-
-// decode_kernel's ring: 2 KB without a mirror (8 KB table + 2 KB ring =
-// 10 KB of LDS per wave, 16 waves per CU), 512-byte chunks read with one
-// 8-byte load per lane.  A half round (4 sub-steps) reads at most 512 bytes;
-// each half round stores the chunk its slot fetched a round earlier and
-// fetches the next chunk if it will fit when stored (front < cur + 1536),
-// else re-fetches the newest chunk.  Two slots alternate by half round.  The
-// stored frontier then stays at least 512 bytes ahead of the words a half
-// round reads, and a store never overwrites unread words.
-constexpr uint32_t kDecRingBytes = 2048;
-constexpr uint32_t kDecChunk = 512;
-
-struct RingD {
-  uint32_t len;
-  uint32_t front;
-  uint32_t pos[2];
-  uint2 pv[2];
-};
-
-template <int X>
-__device__ __forceinline__ void ringd_half(RingD &rg, uint8_t *ring, const uint8_t *sec, uint32_t cur) {
-  const uint32_t lane = lane_id();
-  *(uint2 *)(ring + ((rg.pos[X] + 8 * lane) & (kDecRingBytes - 1))) = rg.pv[X];
-  asm volatile("" ::: "memory");  // the ring stores stay before the half round's ring reads
-  rg.front += rg.front < cur + 3 * kDecChunk ? kDecChunk : 0;
-  rg.pos[X] = rg.front - kDecChunk;
-  const uint32_t o = rg.pos[X] + 8 * lane;
-  rg.pv[X] = *(const uint2 *)(sec + (o + 8 <= rg.len ? o : rg.len - 8));
 }
 
 template <int E>
@@ -1919,12 +2018,12 @@ struct DecStream {
   uint32_t be, nb;
   Geom g;
 };
-// Checks stream c's header h (words: magic | version, dtype, probability
+// Checks stream c's header hv (words: magic | version, dtype, probability
 // bits, flags | block elements | blocks | elements (2) | total bytes (2))
 // and sets up its geometry; builds the stream-wide lookup table.
 template <int DT, bool SHARED>
-__device__ bool open_stream(const DecodeArgs &a, uint64_t c, const Hdr &h, DecStream &st, uint32_t *lut,
-                            uint16_t *cum_s, uint16_t *f_s) {
+__device__ bool open_stream(const DecodeArgs &a, uint64_t c, const Hdr &hv, DecStream &st, uint32_t *lut) {
+  const Hdr h = uniform_hdr(hv);
   constexpr int E = (DT == 2) ? 4 : 2;
   const bool chunked = a.bpc != 0;
   st.s = a.in + (chunked ? c * a.slot_bytes : 0);
@@ -1958,7 +2057,7 @@ __device__ bool open_stream(const DecodeArgs &a, uint64_t c, const Hdr &h, DecSt
   ok = ok && total >= g.coded_off;
   if (SHARED && ok && nb > 0) {
     // one lookup table for every block of the stream
-    ok = build_lut_shared(mode == 1 ? (const uint16_t *)(s + table_off) : a.table, lut, cum_s, f_s);
+    ok = build_lut_shared(mode == 1 ? (const uint16_t *)(s + table_off) : a.table, lut);
     __syncthreads();
   }
   st.be = be;
@@ -1979,9 +2078,7 @@ __global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
   constexpr int E = (DT == 2) ? 4 : 2;
   constexpr int NW = 4 * (E / 2);
   __shared__ uint32_t lut[kM];
-  __shared__ __align__(16) uint8_t ring[kDecRingBytes];
-  // the table-build scratch (cum, f) lives in the ring before the ring fills
-  uint16_t *cum_s = (uint16_t *)ring, *f_s = (uint16_t *)ring + 256;
+  __shared__ __align__(16) uint8_t ring[kRingBytes];
   const uint32_t lane = lane_id();
   DecStream st;
   uint64_t cur = 0, n_work = 0;
@@ -1990,7 +2087,7 @@ __global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
     // one stream
     Hdr h = {};
     if (a.in_bytes >= kHeaderBytes) h = load_hdr(a.in);
-    ok = open_stream<DT, SHARED>(a, 0, h, st, lut, cum_s, f_s);
+    ok = open_stream<DT, SHARED>(a, 0, h, st, lut);
     if (!ok) {
       if (blockIdx.x == 0 && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
       return;
@@ -2041,7 +2138,7 @@ __global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
       b = (uint32_t)(gb - q * a.bpc);
       if (c != cur) {
         cur = c;
-        ok = open_stream<DT, SHARED>(a, c, here.h, st, lut, cum_s, f_s);
+        ok = open_stream<DT, SHARED>(a, c, here.h, st, lut);
       }
       if (!ok) {
         if (b == 0 && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
@@ -2055,8 +2152,8 @@ __global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
     const uint32_t be = st.be;
     const uint64_t total = st.total;
     const uint8_t *raw_plane = s + g.raw_off;
-    const uint32_t d = here.d;
-    const uint64_t start = b ? 16ull * (here.dp & ~kStoredBit) : 0;
+    const uint32_t d = uniform(here.d);
+    const uint64_t start = b ? 16ull * (uniform(here.dp) & ~kStoredBit) : 0;
     const uint64_t end = 16ull * (d & ~kStoredBit);
     const uint64_t blk0 = (uint64_t)b * be;
     const uint32_t n_b = (uint32_t)((st.n - blk0) < be ? (st.n - blk0) : be);
@@ -2068,8 +2165,8 @@ __global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
     if (!bad && stored && len < n_b) bad = true;
     // The start of a coded section in one round of loads: the states, the
     // presence bits and frequencies, and the 2048 bytes that follow the
-    // fixed part (the first three ring chunks start within its first 512:
-    // the words begin at most 2 x 256 bytes of frequencies in).  Sections
+    // fixed part (the first three chunks of words start within its first
+    // 512: the words begin at most 2 x 256 bytes of frequencies in).  Sections
     // are 16-byte units, so a 16-byte load is either whole inside it or
     // skipped.
     constexpr uint32_t P0 = SHARED ? kSharedSectionFixed : kSectionFixed;
@@ -2120,7 +2217,7 @@ __global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
         continue;
       }
     } else {
-      if (!build_lut_pre(pbyte, pfa, len, lut, cum_s, f_s, k)) {
+      if (!build_lut_pre(pbyte, pfa, len, lut, k)) {
         if (lane == 0) report(a.dstatus, UZIP_ECORRUPT);
         continue;
       }
@@ -2129,135 +2226,93 @@ __global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
     const uint32_t x0 = x;  // checked at the end of the block: no wait for it here
     const uint32_t wb = SHARED ? kSharedSectionFixed : kSectionFixed + 2 * k;  // section offset of word 0
     const uint32_t w_avail = (len - wb) / 2;
-    RingD rg;
-    rg.len = len;
-    {
-      // section bytes [P0, P0 + 2048) fill the ring (which held the table
-      // build's scratch until now), so it holds the three chunks from the
-      // word start's 16-byte unit on; the third chunk is also the first
-      // pending refill
-      const uint32_t base = wb & ~15u;
-      const uint32_t o0 = P0 + 32 * lane;
-      *(uint4 *)(ring + (o0 & (kDecRingBytes - 1))) = pre0;
-      *(uint4 *)(ring + ((o0 + 16) & (kDecRingBytes - 1))) = pre1;
-      wave_lds_fence();
-      rg.front = base + 3 * kDecChunk;
-      rg.pos[0] = rg.pos[1] = base + 2 * kDecChunk;
-      rg.pv[0] = rg.pv[1] = *(const uint2 *)(ring + ((base + 2 * kDecChunk + 8 * lane) & (kDecRingBytes - 1)));
-    }
+    WordRing rg;
+    ring_open(rg, ring, lut, sec, len, wb, P0, pre0, pre1);
     __syncthreads();
-    uint32_t p = 0, rb = wb & (kDecRingBytes - 1);
+    DecState ds = dec_state(x, lut);
     const uint32_t full = n_b / kRound;
     uint8_t *outp = st.out + blk0 * E;
     const uint8_t *rawp = raw_plane + blk0 * (E - 1);
-    uint32_t rawA[6] = {0, 0, 0, 0, 0, 0}, rawB[6] = {0, 0, 0, 0, 0, 0};
-    // round 0's raw bytes; with no full round a dummy load of the stream
-    // header, so that the loop below is always entered with the same loads
-    // in flight and waits only for what it uses
-    load_raw_full<E>(full > 0 ? rawp : s, full > 0 ? kPerLane * lane : 0, rawA);
-    // round 1's (clamped to a full round) likewise
-    load_raw_full<E>(full > 0 ? rawp : s, full > 1 ? (kRound + kPerLane * lane) : (full > 0 ? kPerLane * lane : 0),
-                     rawB);
-    // one more memory operation in flight, standing in for the store that
-    // ends every round, so that both ways into the loops match
-    const uint32_t pad_load = *(const uint32_t *)(s + 4 * lane);
+    // Full rounds, four per iteration.  A round decodes its symbols and, in
+    // the shadow of its LDS reads, merges and stores the round before; its
+    // raw bytes are loaded two rounds ahead of its own decoding, three ahead
+    // of their use (four buffers, no register is copied).
     uint32_t r = 0;
-    // full rounds, four per iteration with four raw buffers: each round's
-    // raw bytes are loaded two rounds before their use
-    uint32_t rawC[6] = {0, 0, 0, 0, 0, 0}, rawD[6] = {0, 0, 0, 0, 0, 0};
-    auto clampr = [&](uint32_t q) { return q < full ? q : full - 1; };
-    for (; r + 4 <= full; r += 4) {
-      if ((r & 15u) == 0) {
-        // a wave's priority steps down with every 16 rounds of a block it
-        // decodes and wraps after four steps: a SIMD issues for its oldest
-        // wave first, and with equal shares the waves that arrived last on a
-        // SIMD would finish last (the fourth ~10% after the first); a wave
-        // that lags gets the issue slots until it has caught up (1 GiB
-        // buffer 0.413 -> 0.407 ms, its chunk streams 0.425 -> 0.421 ms,
-        // interleaved A/B)
-        switch ((r >> 4) & 3u) {
-          case 0: __builtin_amdgcn_s_setprio(3); break;
-          case 1: __builtin_amdgcn_s_setprio(2); break;
-          case 2: __builtin_amdgcn_s_setprio(1); break;
-          default: __builtin_amdgcn_s_setprio(0); break;
+    uint32_t raw0[6], raw1[6], raw2[6], raw3[6], ea[kPerLane], eb[kPerLane];
+#pragma unroll
+    for (int q = 0; q < (int)kPerLane; ++q) ea[q] = eb[q] = 0;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) raw0[q] = raw1[q] = raw2[q] = raw3[q] = 0;
+    auto round = [&](uint32_t rr, uint32_t (&e)[kPerLane], const uint32_t (&ep)[kPerLane],
+                     const uint32_t (&rawp_)[6], uint32_t (&rawn)[6], bool prev) {
+      uint32_t w[NW];
+      ring_land(rg);
+      load_raw_full<E>(rawp, (rr + 2 < full ? rr + 2 : full - 1) * kRound + kPerLane * lane, rawn);
+#pragma unroll
+      for (uint32_t t = 0; t < kPerLane; ++t) {
+        if (t % (kPerLane / 2) == 0) ring_fill(rg, ring, lut);
+        e[t] = decode_step<true>(ds, true, lut, ring, rg.q, [&]() {
+          if (t < 4) {
+            merge_quarter<DT>((int)t, ep, rawp_, w);
+            // (here, not sunk to the store)
+            if constexpr (DT <= 1) {
+              asm volatile("" : "+v"(w[t]));
+            } else if (t & 1) {
+#pragma unroll
+              for (int q = 0; q < NW / 2; ++q) asm volatile("" : "+v"(w[NW / 2 * (t >> 1) + q]));
+            }
+          }
+          if (t == 4 && prev) store_words<E, true>(outp, (rr - 1) * kRound + kPerLane * lane, 8, w);
+        });
+      }
+    };
+    if (full >= 4) {
+      load_raw_full<E>(rawp, kPerLane * lane, raw0);
+      load_raw_full<E>(rawp, kRound + kPerLane * lane, raw1);
+      for (; r + 4 <= full; r += 4) {
+        if ((r & 15u) == 0) {
+          // a wave's priority steps down with every 16 rounds of a block it
+          // decodes and wraps after four steps: a SIMD issues for its oldest
+          // wave first, and with equal shares the waves that arrived last on a
+          // SIMD would finish last (the fourth ~10% after the first); a wave
+          // that lags gets the issue slots until it has caught up (1 GiB
+          // buffer 0.413 -> 0.407 ms, its chunk streams 0.425 -> 0.421 ms,
+          // interleaved A/B)
+          switch ((r >> 4) & 3u) {
+            case 0: __builtin_amdgcn_s_setprio(3); break;
+            case 1: __builtin_amdgcn_s_setprio(2); break;
+            case 2: __builtin_amdgcn_s_setprio(1); break;
+            default: __builtin_amdgcn_s_setprio(0); break;
+          }
         }
-      }
-      uint32_t e[kPerLane], w[NW];
-#define UZIP_DEC_ROUND(RAWUSE, RAWLOAD, DR, AHEAD)                                              \
-  ringd_half<0>(rg, ring, sec, wb + 2 * p);                                                     \
-  load_raw_full<E>(rawp, clampr(r + (AHEAD)) * kRound + kPerLane * lane, RAWLOAD);              \
-  _Pragma("unroll") for (uint32_t t = 0; t < kPerLane; ++t) {                                   \
-    if (t == kPerLane / 2) ringd_half<1>(rg, ring, sec, wb + 2 * p);                            \
-    e[t] = decode_step_ring<true, kDecRingBytes, false>(x, true, lut, ring, rb, p);             \
-  }                                                                                             \
-  merge_entries<DT>(e, RAWUSE, w);                                                              \
-  store_words<E, true>(outp, (r + (DR)) * kRound + kPerLane * lane, 8, w);
-      UZIP_DEC_ROUND(rawA, rawC, 0, 2)
-      UZIP_DEC_ROUND(rawB, rawD, 1, 3)
-      UZIP_DEC_ROUND(rawC, rawA, 2, 4)
-      UZIP_DEC_ROUND(rawD, rawB, 3, 5)
-#undef UZIP_DEC_ROUND
-    }
-    // full rounds, two per iteration with ping-pong raw registers: every
-    // load is issued a round before its use and no register is copied
-    // the rest in twos (rawA, rawB hold rounds r, r + 1 here)
-    for (; r + 2 <= full; r += 2) {
-      ringd_half<0>(rg, ring, sec, wb + 2 * p);
-      load_raw_full<E>(rawp, (r + 1) * kRound + kPerLane * lane, rawB);
-      uint32_t e[kPerLane];
-#pragma unroll
-      for (uint32_t t = 0; t < kPerLane; ++t) {
-        if (t == kPerLane / 2) ringd_half<1>(rg, ring, sec, wb + 2 * p);
-        e[t] = decode_step_ring<true, kDecRingBytes, false>(x, true, lut, ring, rb, p);
+        round(r, ea, eb, raw3, raw2, r > 0);
+        round(r + 1, eb, ea, raw0, raw3, true);
+        round(r + 2, ea, eb, raw1, raw0, true);
+        round(r + 3, eb, ea, raw2, raw1, true);
       }
       uint32_t w[NW];
-      merge_entries<DT>(e, rawA, w);
-      store_words<E, true>(outp, r * kRound + kPerLane * lane, 8, w);
-
-      ringd_half<0>(rg, ring, sec, wb + 2 * p);
-      const uint32_t rn = (r + 2 < full) ? r + 2 : r + 1;  // always a full round: no branch around the load
-      load_raw_full<E>(rawp, rn * kRound + kPerLane * lane, rawA);
-#pragma unroll
-      for (uint32_t t = 0; t < kPerLane; ++t) {
-        if (t == kPerLane / 2) ringd_half<1>(rg, ring, sec, wb + 2 * p);
-        e[t] = decode_step_ring<true, kDecRingBytes, false>(x, true, lut, ring, rb, p);
-      }
-      merge_entries<DT>(e, rawB, w);
-      store_words<E, true>(outp, (r + 1) * kRound + kPerLane * lane, 8, w);
+      merge_entries<DT>(eb, raw3, w);
+      store_words<E, true>(outp, (r - 1) * kRound + kPerLane * lane, 8, w);
     }
-    if (r < full) {  // odd number of full rounds: rawA holds round r
-      ringd_half<0>(rg, ring, sec, wb + 2 * p);
-      uint32_t e[kPerLane];
-#pragma unroll
-      for (uint32_t t = 0; t < kPerLane; ++t) {
-        if (t == kPerLane / 2) ringd_half<1>(rg, ring, sec, wb + 2 * p);
-        e[t] = decode_step_ring<true, kDecRingBytes, false>(x, true, lut, ring, rb, p);
-      }
-      uint32_t w[NW];
-      merge_entries<DT>(e, rawA, w);
-      store_words<E, true>(outp, r * kRound + kPerLane * lane, 8, w);
-      ++r;
-    }
-    if (r < rounds) {  // partial last round
-      ringd_half<0>(rg, ring, sec, wb + 2 * p);
+    // up to three more full rounds and a partial one
+    for (; r < rounds; ++r) {
       const uint32_t i0 = r * kRound + kPerLane * lane;
       const uint32_t valid = i0 < n_b ? (n_b - i0 < 8 ? n_b - i0 : 8) : 0;
-      uint32_t e[kPerLane];
+      uint32_t raw[6] = {0, 0, 0, 0, 0, 0};
+      load_raw<E>(raw_plane, blk0 + i0, valid, raw);
+      ring_land(rg);
 #pragma unroll
       for (uint32_t t = 0; t < kPerLane; ++t) {
-        if (t == kPerLane / 2) ringd_half<1>(rg, ring, sec, wb + 2 * p);
-        e[t] = decode_step_ring<false, kDecRingBytes, false>(x, t < valid, lut, ring, rb, p);
+        if (t % (kPerLane / 2) == 0) ring_fill(rg, ring, lut);
+        ea[t] = decode_step<false>(ds, t < valid, lut, ring, rg.q, []() {});
       }
       if (valid > 0) {
-        uint32_t raw[6];
-        load_raw<E>(raw_plane, blk0 + i0, valid, raw);
         uint32_t w[NW];
-        merge_entries<DT>(e, raw, w);
-        store_words<E>(st.out, blk0 + i0, valid, w);
+        merge_entries<DT>(ea, raw, w);
+        store_words<E, true>(st.out, blk0 + i0, valid, w);
       }
     }
-    asm volatile("" ::"v"(pad_load));
-    if (x != kStateLo || p > w_avail || x0 < kStateLo || x0 >= 0x80000000u) bad = true;
+    if (!dec_at_start(ds, lut) || ring_used(rg, wb) > w_avail || x0 < kStateLo || x0 >= 0x80000000u) bad = true;
     if (__any(bad) && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
     __syncthreads();
   }
@@ -2277,7 +2332,7 @@ __global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
 // barrier per round suffices.
 // ---------------------------------------------------------------------------
 constexpr int kReduceGroup = 8;
-constexpr uint32_t kDecLds = kLutBytes + kRingBytes + kRingMirror;  // per decoding wave
+constexpr uint32_t kDecLds = kLutBytes + kRingBytes;  // per decoding wave
 
 struct ReduceArgs {
   const uint8_t *ins[kReduceGroup];
@@ -2307,7 +2362,7 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_decode_kernel(
   constexpr int E = (DT == 2) ? 4 : 2;
   constexpr int NW = 4 * (E / 2);
   extern __shared__ __align__(16) uint8_t smem_base[];
-  const uint32_t wave = threadIdx.x >> 6;
+  const uint32_t wave = uniform(threadIdx.x >> 6);
   const uint32_t lane = lane_id();
   const int n_in = a.n_in;
   const bool decoder = (int)wave < n_in;
@@ -2326,16 +2381,13 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_decode_kernel(
   uint8_t *ring = smem_base + wave * kDecLds + kLutBytes;
   uint32_t mode = kBad;
   const uint8_t *sec = nullptr, *raw_plane = nullptr;
-  uint32_t x = kStateLo, x0 = kStateLo, p = 0, rb = 0, wb = 0, w_avail = 0;
-  Ring rg;
-  rg.written = 0;
-  rg.len = 16;
-  rg.pv = make_uint4(0, 0, 0, 0);
+  uint32_t x0 = kStateLo, wb = 0, w_avail = 0;
+  DecState ds = {};
+  WordRing rg = {};
   if (decoder) {
-    mode = open_input_block<DT>(a.ins[wave], a.in_bytes[wave], a.n, be, b, n_b, lut, ring, sec, raw_plane, x, wb,
+    mode = open_input_block<DT>(a.ins[wave], a.in_bytes[wave], a.n, be, b, n_b, lut, ring, sec, raw_plane, x0, wb,
                                 w_avail, rg);
-    x0 = x;
-    rb = wb & (kRingBytes - 1);
+    if (mode == kCoded) ds = dec_state(x0, lut);
     if (mode == kBad && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
   } else {
     for (uint32_t i = lane; i < kHistReplicas * kHistStride; i += 64) hist[i] = 0;
@@ -2352,14 +2404,20 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_decode_kernel(
 #pragma unroll
       for (int q = 0; q < NW; ++q) w[q] = 0;
       if (mode == kCoded) {
-        ring_maintain(rg, ring, sec, wb + 2 * p);
         uint32_t e[kPerLane];
+        ring_land(rg);
         if (r < full) {
 #pragma unroll
-          for (uint32_t t = 0; t < kPerLane; ++t) e[t] = decode_step_ring<true>(x, true, lut, ring, rb, p);
+          for (uint32_t t = 0; t < kPerLane; ++t) {
+            if (t % (kPerLane / 2) == 0) ring_fill(rg, ring, lut);
+            e[t] = decode_step<true>(ds, true, lut, ring, rg.q, []() {});
+          }
         } else {
 #pragma unroll
-          for (uint32_t t = 0; t < kPerLane; ++t) e[t] = decode_step_ring<false>(x, t < valid, lut, ring, rb, p);
+          for (uint32_t t = 0; t < kPerLane; ++t) {
+            if (t % (kPerLane / 2) == 0) ring_fill(rg, ring, lut);
+            e[t] = decode_step<false>(ds, t < valid, lut, ring, rg.q, []() {});
+          }
         }
         uint32_t raw[6] = {0, 0, 0, 0, 0, 0};
         load_raw<E>(raw_plane, blk0 + i0, valid, raw);
@@ -2436,7 +2494,7 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_decode_kernel(
   }
   __syncthreads();
   if (decoder && mode == kCoded) {
-    const bool bad = x != kStateLo || p > w_avail || x0 < kStateLo || x0 >= 0x80000000u;
+    const bool bad = !dec_at_start(ds, lut) || ring_used(rg, wb) > w_avail || x0 < kStateLo || x0 >= 0x80000000u;
     if (__any(bad) && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
   }
   if (!decoder && a.last) {
@@ -2473,7 +2531,7 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
   extern __shared__ __align__(16) uint8_t smem_base[];
   __shared__ uint32_t s_block;
   typedef __attribute__((address_space(3))) uint16_t lds16_t;
-  const uint32_t wave = threadIdx.x >> 6;
+  const uint32_t wave = uniform(threadIdx.x >> 6);
   const uint32_t lane = lane_id();
   const int n_in = r.n_in;
   const bool decoder = (int)wave < n_in;
@@ -2502,16 +2560,13 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
   uint8_t *ring = smem_base + wave * kDecLds + kLutBytes;
   uint32_t mode = kBad;
   const uint8_t *sec = nullptr, *raw_plane = nullptr;
-  uint32_t x = kStateLo, x0 = kStateLo, p = 0, rb = 0, wb = 0, w_avail = 0;
-  Ring rg;
-  rg.written = 0;
-  rg.len = 16;
-  rg.pv = make_uint4(0, 0, 0, 0);
+  uint32_t x0 = kStateLo, wb = 0, w_avail = 0;
+  DecState ds = {};
+  WordRing rg = {};
   if (decoder) {
-    mode = open_input_block<DT>(r.ins[wave], r.in_bytes[wave], r.n, be, b, n_b, lut, ring, sec, raw_plane, x, wb,
+    mode = open_input_block<DT>(r.ins[wave], r.in_bytes[wave], r.n, be, b, n_b, lut, ring, sec, raw_plane, x0, wb,
                                 w_avail, rg);
-    x0 = x;
-    rb = wb & (kRingBytes - 1);
+    if (mode == kCoded) ds = dec_state(x0, lut);
     if (mode == kBad && lane == 0) report(r.dstatus, UZIP_ECORRUPT);
   }
   uint32_t *h = hist + (lane & (kHistReplicas - 1)) * kHistStride;
@@ -2540,14 +2595,20 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
       for (int t = 0; t < NW; ++t) w[t] = 0;
       if (mode != kBad && q + 1 < rounds) load_raw_round(q + 1, nxt);
       if (mode == kCoded) {
-        ring_maintain(rg, ring, sec, wb + 2 * p);
         uint32_t e[kPerLane];
+        ring_land(rg);
         if (q < full) {
 #pragma unroll
-          for (uint32_t t = 0; t < kPerLane; ++t) e[t] = decode_step_ring<true>(x, true, lut, ring, rb, p);
+          for (uint32_t t = 0; t < kPerLane; ++t) {
+            if (t % (kPerLane / 2) == 0) ring_fill(rg, ring, lut);
+            e[t] = decode_step<true>(ds, true, lut, ring, rg.q, []() {});
+          }
         } else {
 #pragma unroll
-          for (uint32_t t = 0; t < kPerLane; ++t) e[t] = decode_step_ring<false>(x, t < valid, lut, ring, rb, p);
+          for (uint32_t t = 0; t < kPerLane; ++t) {
+            if (t % (kPerLane / 2) == 0) ring_fill(rg, ring, lut);
+            e[t] = decode_step<false>(ds, t < valid, lut, ring, rg.q, []() {});
+          }
         }
         merge_entries<DT>(e, cur, w);
       } else if (mode == kStored && valid > 0) {
@@ -2618,14 +2679,13 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
     round_body(q + 1, rawB, rawA);
   }
   if (q < rounds) round_body(q, rawA, rawB);
-  __syncthreads();
-  if (decoder) {
-    if (mode == kCoded) {
-      const bool bad = x != kStateLo || p > w_avail || x0 < kStateLo || x0 >= 0x80000000u;
-      if (__any(bad) && lane == 0) report(r.dstatus, UZIP_ECORRUPT);
-    }
-    return;
+  if (decoder && mode == kCoded) {
+    // (before the barrier: the coding pass takes the tables' place)
+    const bool bad = !dec_at_start(ds, lut) || ring_used(rg, wb) > w_avail || x0 < kStateLo || x0 >= 0x80000000u;
+    if (__any(bad) && lane == 0) report(r.dstatus, UZIP_ECORRUPT);
   }
+  __syncthreads();
+  if (decoder) return;
 
   // ---- the reducing wave codes the block (the decoding waves have ended) ----
   uint4 *enc = (uint4 *)(smem_base + r.lds_enc);
@@ -3113,16 +3173,14 @@ uint32_t fused_layout(int n_in, uint32_t E, uint32_t block_elems, ReduceArgs *r)
   const uint32_t dec = (uint32_t)n_in * kDecLds;
   uint32_t o = (dec > stage ? dec : stage);
   o = (o + 15u) & ~15u;
-  const uint32_t slabs = o;
-  o += 2u * (uint32_t)n_in * kRound * E;
+  // the coding pass's table and trash slots take the slabs' place
+  const uint32_t slabs = o, enc = o, trash = o + kEncTableBytes;
+  const uint32_t slab_bytes = 2u * (uint32_t)n_in * kRound * E;
+  o += slab_bytes > kEncTableBytes + kTrashBytes ? slab_bytes : kEncTableBytes + kTrashBytes;
   const uint32_t hist = o;
   o += kHistBytes;
   const uint32_t syms = o;
   o += (block_elems + 15u) & ~15u;
-  const uint32_t enc = o;
-  o += kEncTableBytes;
-  const uint32_t trash = o;
-  o += kTrashBytes;
   if (o + 1024 > kLdsMax) return 0;  // (the kernel's own static bytes besides)
   if (r != nullptr) {
     r->lds_slabs = slabs;

@@ -124,6 +124,18 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 // exclusive prefix sum over lanes
 __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v) { return wave_incl_scan(v) - v; }
 
+// exclusive running maximum over lanes (0 in lane 0)
+__device__ __forceinline__ uint32_t wave_excl_max(uint32_t v) {
+  v = max(v, dpp_mov<kRowShr1>(v));
+  v = max(v, dpp_mov<kRowShr2>(v));
+  v = max(v, dpp_mov<kRowShr4>(v));
+  v = max(v, dpp_mov<kRowShr8>(v));
+  v = max(v, dpp_mov<kRowBcast15, 0xA>(v));
+  v = max(v, dpp_mov<kRowBcast31, 0xC>(v));
+  const uint32_t u = __shfl_up(v, 1);
+  return lane_id() ? u : 0u;
+}
+
 __device__ inline uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // ---- element transform (section 2.1.2, Step 1) ----
@@ -181,17 +193,22 @@ __device__ inline void split8x2(const uint32_t w[4], Group &g) {
   g.raw[1] = __builtin_amdgcn_perm(r[3], r[2], 0x06040200u);
 }
 
-__device__ inline void merge8x2(const uint32_t sym[2], const uint32_t raw[2], uint32_t w[4]) {
+// four units (one half of a group): their symbols and raw bytes -> two words
+__device__ inline void merge8x2_half(uint32_t sym, uint32_t raw, uint32_t w[2]) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
+  for (int q = 0; q < 2; ++q) {
     // units 2q, 2q + 1: each unit byte twice, then one nibble per value byte
-    const uint32_t sel = (q & 1) ? 0x03030202u : 0x01010000u;
-    const uint32_t sp = __builtin_amdgcn_perm(0u, sym[q >> 1], sel);
-    const uint32_t rp = __builtin_amdgcn_perm(0u, raw[q >> 1], sel);
+    const uint32_t sel = q ? 0x03030202u : 0x01010000u;
+    const uint32_t sp = __builtin_amdgcn_perm(0u, sym, sel);
+    const uint32_t rp = __builtin_amdgcn_perm(0u, raw, sel);
     const uint32_t sn = (sp & 0x000F000Fu) | ((sp >> 4) & 0x0F000F00u);
     const uint32_t rn = (rp & 0x000F000Fu) | ((rp >> 4) & 0x0F000F00u);
     w[q] = ((rn << 4) & 0x80808080u) | (sn << 3) | (rn & 0x07070707u);
   }
+}
+__device__ inline void merge8x2(const uint32_t sym[2], const uint32_t raw[2], uint32_t w[4]) {
+  merge8x2_half(sym[0], raw[0], w);
+  merge8x2_half(sym[1], raw[1], w + 2);
 }
 
 __device__ inline void split32(const uint32_t w[8], Group &g) {
@@ -210,20 +227,21 @@ __device__ inline void split32(const uint32_t w[8], Group &g) {
   }
 }
 
+// four fp32 elements (one half of a group): symbols and 12 raw bytes
+__device__ inline void merge32_half(uint32_t sym, const uint32_t raw[3], uint32_t w[4]) {
+  const uint32_t r0 = raw[0], r1 = raw[1], r2 = raw[2];
+  const uint32_t a = r0 & 0xFFFFFFu;
+  const uint32_t b = (r0 >> 24) | ((r1 & 0xFFFFu) << 8);
+  const uint32_t c = (r1 >> 16) | ((r2 & 0xFFu) << 16);
+  const uint32_t d = r2 >> 8;
+  w[0] = rotr32(a | (sym << 24));
+  w[1] = rotr32(b | ((sym >> 8) << 24));
+  w[2] = rotr32(c | ((sym >> 16) << 24));
+  w[3] = rotr32(d | ((sym >> 24) << 24));
+}
 __device__ inline void merge32(const uint32_t sym[2], const uint32_t raw[6], uint32_t w[8]) {
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    uint32_t r0 = raw[3 * h], r1 = raw[3 * h + 1], r2 = raw[3 * h + 2];
-    uint32_t a = r0 & 0xFFFFFFu;
-    uint32_t b = (r0 >> 24) | ((r1 & 0xFFFFu) << 8);
-    uint32_t c = (r1 >> 16) | ((r2 & 0xFFu) << 16);
-    uint32_t d = r2 >> 8;
-    uint32_t s = sym[h];
-    w[4 * h + 0] = rotr32(a | (s << 24));
-    w[4 * h + 1] = rotr32(b | ((s >> 8) << 24));
-    w[4 * h + 2] = rotr32(c | ((s >> 16) << 24));
-    w[4 * h + 3] = rotr32(d | ((s >> 24) << 24));
-  }
+  merge32_half(sym[0], raw, w);
+  merge32_half(sym[1], raw + 3, w + 4);
 }
 
 __device__ inline uint32_t sym_at(const uint32_t sym[2], uint32_t t) {
