@@ -57,7 +57,6 @@ using namespace uzip;
 namespace {
 
 constexpr int kMaxInputs = 16;
-constexpr uint32_t kTrashBytes = 256;  // encoder: slots for non-emitted words (2 bytes per lane), free outside coding
 constexpr uint32_t kMinBlockBytes = 4096, kMaxBlockBytes = 4194304;
 
 struct EncodeArgs {
@@ -744,48 +743,78 @@ __device__ __forceinline__ void enc_lookup8_at(uint32_t s0, uint32_t s1, uint4 (
 }
 
 // One encoder sub-step of every lane (rANS coding function with 16-bit
-// renormalisation).  Emitted words go to virtual staging index
-// pos - cnt + rank, compacted across the wave with ballot + mbcnt.
-//
-// enc_step_lds: the whole step lands in the LDS staging area (index v lives
-// at lds[v - lo]); branch-free: every lane stores, lanes that emit nothing
+// renormalisation).  Emitted words are compacted across the wave with ballot
+// and mbcnt into the row of the LDS staging area below the last one, in
+// ascending lanes; branch-free: every lane stores, lanes that emit nothing
 // store into their own trash slot.
-template <bool FULL, bool RANK0>
-__device__ __forceinline__ void enc_step_lds(uint32_t &x, const uint4 e, bool valid, uint32_t &pos,
-                                             __attribute__((address_space(3))) uint16_t *lds_rel,
-                                             __attribute__((address_space(3))) uint16_t *trash) {
-  const bool emit = (FULL || valid) && x >= e.y;
-  const uint64_t m = __ballot(emit);
-  const uint32_t base = pos - (uint32_t)__popcll(m);
-  __attribute__((address_space(3))) uint16_t *dst;
-  if constexpr (RANK0) {
-    // the lane's rank among the emitting lanes, and the wave-uniform row
-    // address formed on the scalar unit (one vector move fewer; the large
-    // blocks' coding loops spill more with it)
-    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    __attribute__((address_space(3))) uint16_t *row = lds_rel + base;
-    dst = emit ? row + rank : trash;
-  } else {
-    const uint32_t v = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
-    dst = emit ? lds_rel + v : trash;
-  }
-  *dst = (uint16_t)x;
-  x = emit ? x >> 16 : x;
-  pos = base;
-  if (FULL || valid) {
-    const uint32_t q = __umulhi(x, e.x) >> (e.z >> 24);
-    x = x + __umul24(q, e.z) + e.w;
-  }
+//
+// What bounds the coding pass is the instructions a wave issues (one in ~5
+// cycles, whatever it depends on, at the two waves a SIMD holds), so the
+// sub-step of a full round is written out: 15 instead of the 17 the compiler
+// makes (a mask is first used two instructions after its compare).  The row's byte address costs two scalar instructions: a row of 64 - z words moves it down by 128 - 2 z, z the lanes that
+// emit nothing, and the 128 goes into the store's offset field.  The state
+// is renormalised by one select of its high half and updated by one
+// multiply-add.  Measured against the compiler's form: 122 -> 104 cycles a
+// sub-step on a lone wave (112 with the count right after the compare: a
+// scalar read of a fresh mask stalls the wave), 256 KiB of bf16 49.3 -> 44.7
+// us, the 1 GiB weight buffer 538 -> 524 us, 512 MiB of KV chunks 325 -> 309.
+//   entry e: {reciprocal, f << 20, (M - f) | shift << 24, cum}
+template <int T>
+__device__ __forceinline__ void enc_step_full(uint32_t &x, const uint4 e, uint32_t &row,
+                                              __attribute__((address_space(3))) uint16_t *trash) {
+  uint32_t n, at, q, z;
+  asm("v_cmp_ge_u32 vcc, %[x], %[ey]\n\t"
+      "v_lshrrev_b32 %[n], 16, %[x]\n\t"
+      "s_nop 0\n\t"
+      "v_cndmask_b32 %[n], %[x], %[n], vcc\n\t"
+      "v_mbcnt_lo_u32_b32 %[at], vcc_lo, 0\n\t"
+      "v_mul_hi_u32 %[q], %[n], %[ex]\n\t"
+      "v_mbcnt_hi_u32_b32 %[at], vcc_hi, %[at]\n\t"
+      "s_bcnt0_i32_b64 %[z], vcc\n\t"
+      "v_lshrrev_b32_sdwa %[q], %[ez], %[q] dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_3 src1_sel:DWORD\n\t"
+      "v_add_u32 %[n], %[n], %[ew]\n\t"
+      "s_lshl1_add_u32 %[row], %[z], %[row]\n\t"
+      "v_mad_u32_u24 %[n], %[q], %[ez], %[n]\n\t"
+      "v_lshl_add_u32 %[at], %[at], 1, %[row]\n\t"
+      "v_cndmask_b32 %[at], %[tr], %[at], vcc"
+      : [n] "=&v"(n), [at] "=&v"(at), [q] "=&v"(q), [z] "=&s"(z), [row] "+s"(row)
+      : [x] "v"(x), [ex] "v"(e.x), [ey] "v"(e.y), [ez] "v"(e.z), [ew] "v"(e.w), [tr] "v"(trash)
+      : "vcc", "scc");
+  ((__attribute__((address_space(3))) uint16_t *)(uintptr_t)at)[64 * T] = (uint16_t)x;
+  x = n;
 }
 
-// One round of 8 sub-steps, backwards.
-template <bool FULL, bool RANK0 = false>
+// One round of 8 sub-steps, backwards.  Virtual staging index pos is at LDS
+// byte rel + 2 pos; trash: this lane's trash slots (one for each sub-step,
+// 128 bytes apart).
+template <bool FULL>
 __device__ __forceinline__ void enc_round(uint32_t &x, const uint4 (&e)[8], uint32_t valid, uint32_t &pos,
-                                          __attribute__((address_space(3))) uint16_t *lds_rel,
-                                          __attribute__((address_space(3))) uint16_t *trash) {
+                                          uint32_t rel, __attribute__((address_space(3))) uint16_t *trash) {
+  typedef __attribute__((address_space(3))) uint16_t lds16_t;
+  if constexpr (FULL) {
+    uint32_t row = uniform(rel + 2 * pos - 128 * kPerLane);
+    enc_step_full<7>(x, e[7], row, trash);
+    enc_step_full<6>(x, e[6], row, trash);
+    enc_step_full<5>(x, e[5], row, trash);
+    enc_step_full<4>(x, e[4], row, trash);
+    enc_step_full<3>(x, e[3], row, trash);
+    enc_step_full<2>(x, e[2], row, trash);
+    enc_step_full<1>(x, e[1], row, trash);
+    enc_step_full<0>(x, e[0], row, trash);
+    pos = (row - rel) >> 1;
+  } else {
 #pragma unroll
-  for (int tt = kPerLane - 1; tt >= 0; --tt)
-    enc_step_lds<FULL, RANK0>(x, e[tt], (uint32_t)tt < valid, pos, lds_rel, trash);
+    for (int t = (int)kPerLane - 1; t >= 0; --t) {
+      const bool on = (uint32_t)t < valid;
+      const bool emit = on && x >= e[t].y;
+      const uint64_t m = __ballot(emit);
+      pos -= (uint32_t)__popcll(m);
+      lds16_t *dst = emit ? (lds16_t *)(uintptr_t)rel + (pos + mbcnt(m)) : trash;
+      *dst = (uint16_t)x;
+      x = emit ? x >> 16 : x;
+      if (on) x = x + __umul24(__umulhi(x, e[t].x) >> (e[t].z >> 24), e[t].z) + e[t].w;
+    }
+  }
 }
 
 // The LDS staging window holds virtual indices [lo, lo + cap) at win[v - lo]
@@ -1155,8 +1184,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
   // variants would spill), 8 KiB for fp32
   constexpr int D = (E == 2) ? (SHARED ? 8 : 16) : 4;
   extern __shared__ __align__(16) uint8_t smem_base[];
-  uint8_t *smem = smem_base + kTrashBytes;  // [trash | encoder table | histogram / staging]
-  uint4 *enc = (uint4 *)smem;  // at LDS byte kTrashBytes: the kernel has no static LDS (the host checks)
+  uint8_t *smem = smem_base;  // [encoder table | histogram / staging]
+  uint4 *enc = (uint4 *)smem;  // at LDS byte 0: the kernel has no static LDS (the host checks)
   uint32_t *hist = (uint32_t *)(smem + kEncTableBytes);
   uint8_t *stage = smem + a.pass2_off;
   uint16_t *stage16 = (uint16_t *)(stage + kStageHead);
@@ -1166,14 +1195,15 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
   // ovf[v] is index v
   uint16_t *ovf = a.slots + (uint64_t)blockIdx.x * a.slot_words + kSlotLead - a.lds_words;
   typedef __attribute__((address_space(3))) uint16_t lds16_t;
-  // one private 2-byte slot per lane for words that are not emitted (64
-  // slots in 32 consecutive words: every bank once)
-  lds16_t *trash = (lds16_t *)smem_base + lane;
+  // private 2-byte slots per lane and sub-step for words that are not
+  // emitted (64 slots in 32 consecutive words: every bank once), in the
+  // staging area's head, which is free while a block is coded
+  lds16_t *trash = (lds16_t *)smem_base + kEncTableBytes / 2 + lane;
   // small blocks: a block's offset is resolved and its section written
   // after the next block's first pass, so the wait for slower predecessors
   // overlaps streaming.  The staging area then still holds the pending
   // block's image during the first pass: the histogram takes packed 16-bit
-  // counts in the trash slots and encoder table instead, which are free
+  // counts in the encoder table and the first trash slots instead, which are free
   // until the coding pass (the table is built from the counts in place).
   constexpr bool DEFER = SMALL && !REDUCE;
   // larger blocks keep their last 64 rounds' symbols in registers, so the
@@ -1182,7 +1212,8 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
   // 1 GiB bf16 buffer 0.816 -> 0.775 ms, 512 MiB fp16 gradient 0.484 ->
   // 0.480 ms)
   constexpr bool KEEP = !SMALL && !REDUCE;
-  static_assert(kHistReplicas * kPackedHistStride * 4 <= kTrashBytes + kEncTableBytes, "packed histogram");
+  static_assert(kHistReplicas * kPackedHistStride * 4 <= kEncTableBytes + kStageHead - 800, "packed histogram");
+  static_assert(kStageHead >= 128 * kPerLane, "trash slots");
   uint32_t *phist = (uint32_t *)smem_base;
   Fin pend;
   bool have_pend = false;
@@ -1455,9 +1486,10 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
       ((uint32_t *)(stage + kStageHead + 2 * a.lds_words))[i] = 0;
     const uint32_t limit_words = (n_b > hdr) ? (n_b - hdr + 1) / 2 : 0;
     uint32_t pos = a.wcap;  // virtual staging indices [pos, wcap) hold the words written so far
-    // LDS window over virtual indices [lo, lo + lds_words); lds_rel[v] is index v
+    // LDS window over virtual indices [lo, lo + lds_words); index v is at LDS byte rel + 2 v
     uint32_t lo = a.wcap - a.lds_words;
-    lds16_t *lds_rel = (lds16_t *)stage16 - lo;
+    constexpr uint32_t kWords0 = kEncTableBytes + kStageHead;  // LDS byte of the window's first word
+    uint32_t rel = kWords0 - 2 * lo;
     uint32_t spilled = a.wcap;  // indices [spilled, wcap) live in the overflow slot
     uint32_t x = kStateLo;
     bool stored = (limit_words == 0);
@@ -1476,12 +1508,12 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
       const uint32_t sy[2] = {s0, s1};
       uint4 e[8];
       if constexpr (SMALL) {  // (the large blocks' loops spill more with the fixed-address form)
-        enc_lookup8_at<kTrashBytes>(sy[0], sy[1], e);
+        enc_lookup8_at<0>(sy[0], sy[1], e);
       } else {
 #pragma unroll
         for (int tt = 0; tt < 8; ++tt) e[tt] = enc[sym_at(sy, tt)];
       }
-      enc_round<false, SMALL>(x, e, valid, pos, lds_rel, trash);
+      enc_round<false>(x, e, valid, pos, rel, trash);
       if (a.wcap - pos >= limit_words) stored = true;
     }
     if constexpr (SMALL) {
@@ -1495,12 +1527,12 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
               slide_window((lds16_t *)stage16, ovf + lo, a.lds_words, x, pos - lo);
               lo -= x;
               spilled = lo + a.lds_words;
-              lds_rel = (lds16_t *)stage16 - lo;
+              rel = kWords0 - 2 * lo;
             }
             const uint32_t s0 = S.v3[2 * rr], s1 = S.v3[2 * rr + 1];
             uint4 e[8];
-            enc_lookup8_at<kTrashBytes>(s0, s1, e);
-            enc_round<true, true>(x, e, 8, pos, lds_rel, trash);
+            enc_lookup8_at<0>(s0, s1, e);
+            enc_round<true>(x, e, 8, pos, rel, trash);
             if (a.wcap - pos >= limit_words) stored = true;
           }
         }
@@ -1525,12 +1557,12 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
                 slide_window((lds16_t *)stage16, ovf + lo, a.lds_words, x, pos - lo);
                 lo -= x;
                 spilled = lo + a.lds_words;
-                lds_rel = (lds16_t *)stage16 - lo;
+                rel = kWords0 - 2 * lo;
               }
               const uint32_t s0 = S.v3[2 * rr], s1 = S.v3[2 * rr + 1];
               uint4 e[8];
               enc_lookup8(enc, s0, s1, e);
-              enc_round<true>(x, e, 8, pos, lds_rel, trash);
+              enc_round<true>(x, e, 8, pos, rel, trash);
               if (a.wcap - pos >= limit_words) stored = true;
             }
           }
@@ -1554,7 +1586,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
               slide_window((lds16_t *)stage16, ovf + lo, a.lds_words, x, pos - lo);
               lo -= x;
               spilled = lo + a.lds_words;
-              lds_rel = (lds16_t *)stage16 - lo;
+              rel = kWords0 - 2 * lo;
             }
             Group gr;
             split_group<DT>(pb[u], gr);
@@ -1563,7 +1595,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
             load_round<E, true>(src_blk + (uint64_t)(rn >= 0 ? rn : 0) * kRound * E, pb[u]);
             uint4 e[8];
             enc_lookup8(enc, gr.sym[0], gr.sym[1], e);
-            enc_round<true>(x, e, 8, pos, lds_rel, trash);
+            enc_round<true>(x, e, 8, pos, rel, trash);
             if (a.wcap - pos >= limit_words) stored = true;
           }
         }
@@ -1581,14 +1613,14 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
           slide_window((lds16_t *)stage16, ovf + lo, a.lds_words, x, pos - lo);
           lo -= x;
           spilled = lo + a.lds_words;
-          lds_rel = (lds16_t *)stage16 - lo;
+          rel = kWords0 - 2 * lo;
         }
         load_round<E>(src_blk + (uint64_t)(r - 1) * kRound * E, wbuf);
         Group gr;
         split_group<DT>(wa, gr);
         uint4 e[8];
         enc_lookup8(enc, gr.sym[0], gr.sym[1], e);
-        enc_round<true>(x, e, 8, pos, lds_rel, trash);
+        enc_round<true>(x, e, 8, pos, rel, trash);
         if (a.wcap - pos >= limit_words) stored = true;
         if (stored) break;
         if (pos < lo + kRound && lo > 0) {  // the LDS window is full: slide it down
@@ -1596,13 +1628,13 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
           slide_window((lds16_t *)stage16, ovf + lo, a.lds_words, x, pos - lo);
           lo -= x;
           spilled = lo + a.lds_words;
-          lds_rel = (lds16_t *)stage16 - lo;
+          rel = kWords0 - 2 * lo;
         }
         const uint32_t rn = r >= 2 ? (uint32_t)(r - 2) : 0u;
         load_round<E>(src_blk + (uint64_t)rn * kRound * E, wa);
         split_group<DT>(wbuf, gr);
         enc_lookup8(enc, gr.sym[0], gr.sym[1], e);
-        enc_round<true>(x, e, 8, pos, lds_rel, trash);
+        enc_round<true>(x, e, 8, pos, rel, trash);
         if (a.wcap - pos >= limit_words) stored = true;
       }
       if (r == 0 && !stored) {  // wa holds round 0
@@ -1611,13 +1643,13 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
           slide_window((lds16_t *)stage16, ovf + lo, a.lds_words, x, pos - lo);
           lo -= x;
           spilled = lo + a.lds_words;
-          lds_rel = (lds16_t *)stage16 - lo;
+          rel = kWords0 - 2 * lo;
         }
         Group gr;
         split_group<DT>(wa, gr);
         uint4 e[8];
         enc_lookup8(enc, gr.sym[0], gr.sym[1], e);
-        enc_round<true>(x, e, 8, pos, lds_rel, trash);
+        enc_round<true>(x, e, 8, pos, rel, trash);
         if (a.wcap - pos >= limit_words) stored = true;
       }
     }
@@ -2352,7 +2384,7 @@ struct ReduceArgs {
   uint32_t *dstatus;
   // reduce_fused_kernel: byte offsets of its LDS regions (the decoders'
   // tables and rings, later the coding pass's staging area, start at 0)
-  uint32_t lds_slabs, lds_hist, lds_syms, lds_enc, lds_trash;
+  uint32_t lds_slabs, lds_hist, lds_syms, lds_enc;
 };
 
 uint32_t reduce_lds(int n_in, uint32_t E) { return n_in * (kDecLds + 2 * kRound * E) + kHistBytes; }
@@ -2689,8 +2721,8 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
 
   // ---- the reducing wave codes the block (the decoding waves have ended) ----
   uint4 *enc = (uint4 *)(smem_base + r.lds_enc);
-  lds16_t *trash = (lds16_t *)(smem_base + r.lds_trash) + lane;
   uint8_t *stage = smem_base;  // where the lookup tables and rings were
+  lds16_t *trash = (lds16_t *)smem_base + lane;  // (the staging area's head)
   uint16_t *stage16 = (uint16_t *)(stage + kStageHead);
   if (b + 1 == a.n_blocks && lane < 16) {
     // zero padding after the raw plane (pad16 of (E-1) n bytes)
@@ -2706,7 +2738,7 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
   for (uint32_t i = lane; i < kStageTail / 4; i += 64) ((uint32_t *)(stage16 + a.wcap))[i] = 0;
   const uint32_t limit_words = (n_b > hdr) ? (n_b - hdr + 1) / 2 : 0;
   uint32_t pos = a.wcap;  // staging indices [pos, wcap) hold the words so far; the block's words all fit
-  lds16_t *lds_rel = (lds16_t *)stage16;
+  const uint32_t rel = (uint32_t)(uintptr_t)(lds16_t *)smem_base + kStageHead;
   uint32_t xs = kStateLo;
   bool stored = (limit_words == 0);
   if (full < rounds && !stored) {  // the partial last round comes first
@@ -2716,14 +2748,14 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
     const uint32_t sy[2] = {sv.x, sv.y};
     uint4 e[8];
     enc_lookup8(enc, sy[0], sy[1], e);
-    enc_round<false>(xs, e, valid, pos, lds_rel, trash);
+    enc_round<false>(xs, e, valid, pos, rel, trash);
     if (a.wcap - pos >= limit_words) stored = true;
   }
   for (int q2 = (int)full - 1; q2 >= 0 && !stored; --q2) {
     const uint2 sv = *(const uint2 *)(syms + (uint32_t)q2 * kRound + kPerLane * lane);
     uint4 e[8];
     enc_lookup8(enc, sv.x, sv.y, e);
-    enc_round<true>(xs, e, 8, pos, lds_rel, trash);
+    enc_round<true>(xs, e, 8, pos, rel, trash);
     if (a.wcap - pos >= limit_words) stored = true;
   }
   pos = uniform(pos);
@@ -3122,7 +3154,7 @@ uint64_t n_slots(uint64_t n_blocks, uint32_t block_elems) {
 uint32_t encode_lds(uint32_t block_elems) {
   const uint32_t pass1 = kHistBytes;
   const uint32_t pass2 = kStageHead + 2 * stage_words(block_elems) + kStageTail;
-  return kTrashBytes + kEncTableBytes + (pass1 > pass2 ? pass1 : pass2);
+  return kEncTableBytes + (pass1 > pass2 ? pass1 : pass2);
 }
 
 struct EncodeWs {
@@ -3173,10 +3205,10 @@ uint32_t fused_layout(int n_in, uint32_t E, uint32_t block_elems, ReduceArgs *r)
   const uint32_t dec = (uint32_t)n_in * kDecLds;
   uint32_t o = (dec > stage ? dec : stage);
   o = (o + 15u) & ~15u;
-  // the coding pass's table and trash slots take the slabs' place
-  const uint32_t slabs = o, enc = o, trash = o + kEncTableBytes;
+  // the coding pass's table takes the slabs' place
+  const uint32_t slabs = o, enc = o;
   const uint32_t slab_bytes = 2u * (uint32_t)n_in * kRound * E;
-  o += slab_bytes > kEncTableBytes + kTrashBytes ? slab_bytes : kEncTableBytes + kTrashBytes;
+  o += slab_bytes > kEncTableBytes ? slab_bytes : kEncTableBytes;
   const uint32_t hist = o;
   o += kHistBytes;
   const uint32_t syms = o;
@@ -3187,7 +3219,6 @@ uint32_t fused_layout(int n_in, uint32_t E, uint32_t block_elems, ReduceArgs *r)
     r->lds_hist = hist;
     r->lds_syms = syms;
     r->lds_enc = enc;
-    r->lds_trash = trash;
   }
   return o;
 }
