@@ -435,7 +435,7 @@ struct Table {
 // the smallest), cum in ascending symbol order.  Writes the encoder table
 // {reciprocal, f << 20, (M - f) | shift << 24, cum (+2047 if f == 1)}.
 __device__ void enc_entries(const Table &t, uint4 *enc);
-template <bool PACKED = false>
+template <bool PACKED = false, uint32_t REPS = kHistReplicas>
 __device__ void build_enc_table(const uint32_t *hist, uint32_t n_b, uint4 *enc, Table &t) {
   const uint32_t lane = lane_id();
   uint32_t c[4];
@@ -443,7 +443,7 @@ __device__ void build_enc_table(const uint32_t *hist, uint32_t n_b, uint4 *enc, 
   for (int q = 0; q < 4; ++q) {
     uint32_t s = 4 * lane + q, acc = 0;
 #pragma unroll
-    for (uint32_t rep = 0; rep < kHistReplicas; ++rep) {
+    for (uint32_t rep = 0; rep < REPS; ++rep) {
       if constexpr (PACKED)
         acc += (hist[rep * kPackedHistStride + (s & 127u)] >> (16 * (s >> 7))) & 0xFFFFu;
       else
@@ -993,7 +993,7 @@ struct Fin {
   uint32_t A;          // staging-area byte offset of the image
   uint32_t lds_bytes;  // image bytes in LDS; the rest is in the overflow slot
   uint32_t slot_delta; // slot byte = image byte + slot_delta (mod 2^32)
-  const uint8_t *sym_lds;  // fused reduce: the block's symbols in LDS (a STORED block copies them)
+  const uint8_t *sym_lds;  // wide coding: the block's symbols in LDS (a STORED block copies them)
   bool stored, spilled, last;
 };
 
@@ -1020,6 +1020,32 @@ __device__ __forceinline__ void write_section_head(uint8_t *stage, uint32_t A, u
     for (int q = 0; q < 4; ++q)
       if (t.f[q]) h16[144 + rk++] = (uint16_t)t.f[q];
   }
+}
+
+// The header of a stream whose last block's section starts at 16 excl, and
+// its size.
+template <int DT, bool SYS>
+__device__ __forceinline__ void write_stream_head(const EncodeArgs &a, const Fin &f, uint64_t excl) {
+  const uint32_t lane = lane_id();
+  const uint64_t total = f.coded_off + 16 * (excl + f.sec_len / 16);
+  if (lane == 0) {
+    uint32_t hh[8];
+    hh[0] = kMagic;
+    hh[1] = kVersion | ((uint32_t)DT << 8) | (kProbBits << 16) | (a.table_mode << 24);
+    hh[2] = a.block_elems;
+    hh[3] = f.n_blocks;
+    hh[4] = (uint32_t)f.chunk_n;
+    hh[5] = (uint32_t)(f.chunk_n >> 32);
+    hh[6] = (uint32_t)total;
+    hh[7] = (uint32_t)(total >> 32);
+    uint64_t *hp = (uint64_t *)f.sout;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) coh64<SYS>(hp + q, (uint64_t)hh[2 * q + 1] << 32 | hh[2 * q]);
+    if (a.sizes != nullptr) coh64<SYS>(&a.sizes[f.chunk], total);
+  }
+  // zero padding after the directory
+  const uint64_t db = kHeaderBytes + 4ull * f.n_blocks + lane;
+  if (lane < 16 && db < f.dir_end) out8<SYS>(f.sout + db, 0);
 }
 
 // Resolve the block's offset, write its directory entry and section, and for
@@ -1065,13 +1091,6 @@ __device__ __forceinline__ void finish_block(const EncodeArgs &a, const Fin &f, 
         out128<SYS>(sec + 16 * u, o);
       }
     }
-  } else if (f.sym_lds != nullptr) {
-    // STORED, fused reduce: the block's symbol bytes from LDS, zero-padded
-    for (uint32_t u = lane; u < f.sec_len / 16; u += 64) {
-      uint4 o = *(const uint4 *)(f.sym_lds + 16 * u);
-      if (16 * u + 16 > f.n_b) o = mask_bytes(o, f.n_b - 16 * u);
-      out128<SYS>(sec + 16 * u, o);
-    }
   } else {
     // STORED: the block's symbol bytes, zero-padded to 16, re-read from the
     // input (the coding pass consumed the register copy)
@@ -1099,27 +1118,7 @@ __device__ __forceinline__ void finish_block(const EncodeArgs &a, const Fin &f, 
     }
   }
 
-  if (f.last) {
-    const uint64_t total = f.coded_off + 16 * (excl + f.sec_len / 16);
-    if (lane == 0) {
-      uint32_t hh[8];
-      hh[0] = kMagic;
-      hh[1] = kVersion | ((uint32_t)DT << 8) | (kProbBits << 16) | (a.table_mode << 24);
-      hh[2] = a.block_elems;
-      hh[3] = f.n_blocks;
-      hh[4] = (uint32_t)f.chunk_n;
-      hh[5] = (uint32_t)(f.chunk_n >> 32);
-      hh[6] = (uint32_t)total;
-      hh[7] = (uint32_t)(total >> 32);
-      uint64_t *hp = (uint64_t *)f.sout;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) coh64<SYS>(hp + q, (uint64_t)hh[2 * q + 1] << 32 | hh[2 * q]);
-      if (a.sizes != nullptr) coh64<SYS>(&a.sizes[f.chunk], total);
-    }
-    // zero padding after the directory
-    const uint64_t db = kHeaderBytes + 4ull * f.n_blocks + lane;
-    if (lane < 16 && db < f.dir_end) out8<SYS>(f.sout + db, 0);
-  }
+  if (f.last) write_stream_head<DT, SYS>(a, f, excl);
   if (a.flags != nullptr)
     publish_chunk(&a.chunk_cnt[2 * f.chunk + 1], f.n_blocks, &a.flags[2 * f.chunk + 1], a.epoch, failed, !SYS);
 }
@@ -1681,8 +1680,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     f.stored = stored;
     f.spilled = spilled != a.wcap;
     f.last = last_in_chunk;
-    f.sym_lds = nullptr;
-    if (!stored) {
+      if (!stored) {
       // header bytes right before the words: states | bitmap | f[k] (states
       // only with a stream-wide table)
       write_section_head<SHARED>(stage, f.A, x, t);
@@ -1703,6 +1701,283 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
   if constexpr (DEFER) {
     if (have_pend) finish_block<DT, SYS>(a, pend, stage, ovf);
   }
+}
+
+// ---------------------------------------------------------------------------
+// Wide coding: one block per workgroup of several waves.
+//
+// With few blocks a call takes one block's serial time on one wave: 30k
+// cycles of pass 1, 53k of coding (104 a sub-step), 6k of copy-out for a
+// 64 KiB block, the rest of its compute unit idle.  Here every wave takes
+// rounds of pass 1 (symbols to LDS) and units of the copy-out; the 64 states
+// stay one wave's dependent chain, which reads each half round's table
+// entries half a round ahead.  (Splitting the coding too -- one wave updates
+// the states and writes them to LDS, seven place the words from there -- was
+// slower, 117 cycles a sub-step against 104: what the wave saves in
+// instructions it loses to its stores and to the LDS and issue slots the
+// others take.)
+// ---------------------------------------------------------------------------
+constexpr uint32_t kWideWaves = 8;
+constexpr uint32_t kWideReplicas = 16;  // sub-histograms: the waves count at once
+constexpr uint32_t kWideHist = kWideReplicas * kHistStride * 4;
+
+// What the workgroup shares (LDS).
+struct WideShared {
+  uint32_t block;
+  uint32_t hdr, words, stored;        // section bytes before the words, the words, their position
+  uint32_t excl_lo, excl_hi, failed;  // the section's offset (16-byte units)
+};
+
+// One wave codes the block whose n_b symbols are in LDS at `syms` (512 bytes
+// a round) with the entries `enc`: words at LDS byte rel + 2 pos downwards
+// from pos = wcap, which all fit.  Returns the number of words (from
+// limit_words on the block is to be STORED and they are not complete); x:
+// the final states.
+__device__ __forceinline__ uint32_t code_block_lds(const uint8_t *syms, const uint4 *enc, uint32_t n_b, uint32_t rel,
+                                                   uint32_t wcap, uint32_t limit_words,
+                                                   __attribute__((address_space(3))) uint16_t *trash, uint32_t &x) {
+  const uint32_t lane = lane_id();
+  const uint32_t full = n_b / kRound;
+  uint32_t pos = wcap;
+  if (limit_words == 0) return 0;
+  auto sym_round = [&](uint32_t r) { return *(const uint2 *)(syms + r * kRound + kPerLane * lane); };
+  if (full * kRound < n_b) {  // the partial last round comes first
+    const uint32_t i0 = full * kRound + kPerLane * lane;
+    const uint32_t valid = i0 < n_b ? (n_b - i0 < 8 ? n_b - i0 : 8) : 0;
+    const uint2 sv = sym_round(full);
+    uint4 e[8];
+    enc_lookup8(enc, sv.x, sv.y, e);
+    enc_round<false>(x, e, valid, pos, rel, trash);
+    pos = uniform(pos);
+  }
+  if (full == 0 || wcap - pos >= limit_words) return wcap - pos;
+  uint4 e[8];
+  auto look4 = [&](uint32_t sy, int at) {
+#pragma unroll
+    for (int t = 3; t >= 0; --t) e[at + t] = enc[(sy >> (8 * t)) & 0xFFu];
+  };
+  uint2 sv = sym_round(full - 1), svn = sym_round(full > 1 ? full - 2 : 0);
+  look4(sv.y, 4);
+  uint32_t row = uniform(rel + 2 * pos);
+  const uint32_t row_min = uniform(rel + 2 * (wcap - limit_words));
+  for (uint32_t r = full; r-- > 0;) {
+    row -= 128 * kPerLane;
+    look4(sv.x, 0);
+    enc_step_full<7>(x, e[7], row, trash);
+    enc_step_full<6>(x, e[6], row, trash);
+    enc_step_full<5>(x, e[5], row, trash);
+    enc_step_full<4>(x, e[4], row, trash);
+    sv = svn;
+    svn = sym_round(r > 2 ? r - 2 : 0);
+    look4(sv.y, 4);
+    enc_step_full<3>(x, e[3], row, trash);
+    enc_step_full<2>(x, e[2], row, trash);
+    enc_step_full<1>(x, e[1], row, trash);
+    enc_step_full<0>(x, e[0], row, trash);
+    if (row <= row_min) break;
+  }
+  return wcap - ((row - rel) >> 1);
+}
+
+// The section of a block coded (or to be STORED) by a whole workgroup of
+// `threads` threads: image in LDS at stage + f.A, or the symbols at
+// f.sym_lds.  `lead`: the wave that resolves the offset and writes the
+// directory entry and headers.  Every wave calls it.
+template <int DT, bool SYS>
+__device__ __forceinline__ void finish_wide(const EncodeArgs &a, const Fin &f, const uint8_t *stage, WideShared *sh,
+                                            bool lead, uint32_t threads) {
+  const uint32_t lane = lane_id();
+  if (lead) {
+    publish_aggregate(a.status, f.b, f.first_block, f.sec_len / 16, a.ticket[kWsHold]);
+    bool failed;
+    const uint64_t excl = resolve_prefix(a.status, f.b, f.first_block, f.sec_len / 16, a.ticket[kWsSpin],
+                                         a.ticket[kWsHold], a.ticket + kWsError, failed);
+    if (lane == 0) {
+      sh->excl_lo = (uint32_t)excl;
+      sh->excl_hi = (uint32_t)(excl >> 32);
+      sh->failed = failed;
+    }
+  }
+  __syncthreads();
+  const uint64_t excl = (uint64_t)uniform(sh->excl_hi) << 32 | uniform(sh->excl_lo);
+  uint8_t *sec = f.sout + f.coded_off + 16 * excl;
+  if (!f.stored) {
+    const uint32_t *s32 = (const uint32_t *)(stage + (f.A & ~3u));
+    for (uint32_t u = threadIdx.x; u < f.sec_len / 16; u += threads) out128<SYS>(sec + 16 * u, lds_unit(s32, u, f.A & 3u));
+  } else {
+    for (uint32_t u = threadIdx.x; u < f.sec_len / 16; u += threads) {
+      uint4 o = *(const uint4 *)(f.sym_lds + 16 * u);
+      if (16 * u + 16 > f.n_b) o = mask_bytes(o, f.n_b - 16 * u);
+      out128<SYS>(sec + 16 * u, o);
+    }
+  }
+  if (lead) {
+    if (lane == 0)
+      out32<SYS>((uint32_t *)(f.sout + kHeaderBytes + 4 * f.lb),
+                 (f.stored ? kStoredBit : 0u) | (uint32_t)(excl + f.sec_len / 16));
+    if (f.last) write_stream_head<DT, SYS>(a, f, excl);
+  }
+  // every wave's stores complete before the lead counts the block done
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (lead && a.flags != nullptr)
+    publish_chunk(&a.chunk_cnt[2 * f.chunk + 1], f.n_blocks, &a.flags[2 * f.chunk + 1], a.epoch, sh->failed != 0, !SYS);
+}
+
+// encode_wide_kernel: compress and the split-send producer for calls of few
+// blocks (of up to 32768 elements).  One workgroup of eight waves per block,
+// blocks in ticket order.
+template <int DT, bool SYS, bool SHARED>
+__global__ void __launch_bounds__(64 * kWideWaves) encode_wide_kernel(EncodeArgs a) {
+  constexpr int E = (DT == 2) ? 4 : 2;
+  constexpr int NW = 4 * (E / 2);
+  constexpr uint32_t kMine = kRegRounds / kWideWaves;  // rounds of pass 1 per wave
+  typedef __attribute__((address_space(3))) uint16_t lds16_t;
+  extern __shared__ __align__(16) uint8_t smem_base[];
+  uint4 *enc = (uint4 *)smem_base;
+  uint8_t *stage = smem_base + kEncTableBytes;
+  uint16_t *stage16 = (uint16_t *)(stage + kStageHead);
+  uint32_t *hist = (uint32_t *)stage;  // until the block is coded
+  uint8_t *syms = smem_base + a.pass2_off;
+  WideShared *sh = (WideShared *)(syms + kRound * ((a.block_elems + kRound - 1) / kRound));
+  const uint32_t wave = uniform(threadIdx.x >> 6);
+  const uint32_t lane = lane_id();
+
+  if (threadIdx.x == 0) sh->block = take_block(a);
+  if constexpr (!SHARED)
+    for (uint32_t i = threadIdx.x; i < kWideReplicas * kHistStride; i += 64 * kWideWaves) hist[i] = 0;
+  __syncthreads();
+  const uint32_t b = uniform(sh->block);
+  if (b < a.n_blocks) {  // (the grid has exactly one workgroup per block)
+    const uint32_t chunk = b / a.blocks_per_chunk;
+    const uint32_t lb = b - chunk * a.blocks_per_chunk;
+    const uint64_t chunk_first = (uint64_t)chunk * a.chunk_elems;
+    const uint64_t chunk_n = (a.n - chunk_first) < a.chunk_elems ? (a.n - chunk_first) : a.chunk_elems;
+    Geom g = make_geom(chunk_n, a.block_elems, E);
+    const uint64_t dir_end = g.raw_off;
+    g.raw_off += a.table_bytes;
+    g.coded_off += a.table_bytes;
+    uint8_t *sout = a.out + (uint64_t)chunk * a.slot_bytes;
+    const uint64_t blk0 = (uint64_t)lb * a.block_elems;
+    const uint32_t n_b = (uint32_t)((chunk_n - blk0) < a.block_elems ? (chunk_n - blk0) : a.block_elems);
+    const uint32_t rounds = (n_b + kRound - 1) / kRound;
+    const uint32_t full = n_b / kRound;
+    const uint8_t *src = a.in + chunk_first * E;
+    uint8_t *raw_plane = sout + g.raw_off;
+    Table t;
+    t.k = 256;
+    bool bad = false;
+    if constexpr (SHARED) {
+      // the stream's table: every wave checks it, the first builds the entries
+      const uint2 v = *(const uint2 *)(a.table + (uint64_t)chunk * a.table_stride + 4 * lane);
+      t.f[0] = v.x & 0xFFFFu;
+      t.f[1] = v.x >> 16;
+      t.f[2] = v.y & 0xFFFFu;
+      t.f[3] = v.y >> 16;
+      // (one that is not an all-symbol table codes nothing, as in encode_body)
+      bad = __any(t.f[0] == 0 || t.f[1] == 0 || t.f[2] == 0 || t.f[3] == 0) ||
+            wave_sum(t.f[0] + t.f[1] + t.f[2] + t.f[3]) != kM;
+      if (bad && wave == 0 && lane == 0 && a.sizes != nullptr) a.sizes[chunk] = 0;
+    }
+    if (!bad) {
+      // ---- pass 1: rounds wave, wave + 8, ...: all loads under way at once ----
+      uint32_t w[kMine][NW];
+#pragma unroll
+      for (uint32_t i = 0; i < kMine; ++i) {
+        const uint32_t r = wave + kWideWaves * i;
+        if (r < full) load_round<E, true>(src + (blk0 + (uint64_t)r * kRound) * E, w[i]);
+      }
+      uint32_t *h = hist + (lane & (kWideReplicas - 1)) * kHistStride;
+#pragma unroll
+      for (uint32_t i = 0; i < kMine; ++i) {
+        const uint32_t r = wave + kWideWaves * i;
+        if (r < rounds) {
+          const uint32_t i0 = r * kRound + kPerLane * lane;
+          const uint32_t valid = i0 < n_b ? (n_b - i0 < 8 ? n_b - i0 : 8) : 0;
+          if (r >= full) load_words<E>(src, blk0 + i0, valid, w[i]);  // (zero past the end)
+          Group gr;
+          split_group<DT>(w[i], gr);
+          if (r < full) {
+            store_raw_round<E, SYS>(raw_plane + (blk0 + (uint64_t)r * kRound) * (E - 1), gr);
+            if constexpr (!SHARED) hist_add8(h, gr, 8);
+          } else {
+            if (valid > 0) store_raw<E, SYS>(raw_plane, blk0 + i0, valid, gr);
+            if constexpr (!SHARED) hist_add8(h, gr, valid);
+          }
+          *(uint2 *)(syms + i0) = make_uint2(gr.sym[0], gr.sym[1]);
+        }
+      }
+      if (lb + 1 == g.n_blocks && threadIdx.x < 16) {
+        // zero padding after the raw plane (pad16 of (E-1) n bytes)
+        const uint64_t rb = g.raw_off + (uint64_t)(E - 1) * chunk_n + lane;
+        if (rb < g.coded_off) out8<SYS>(sout + rb, 0);
+      }
+      if (a.flags != nullptr) __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      if (wave == 1 && a.flags != nullptr)
+        publish_chunk(&a.chunk_cnt[2 * chunk], g.n_blocks, &a.flags[2 * chunk], a.epoch, false, !SYS);
+      // ---- table and coding: the first wave ----
+      if constexpr (!SHARED) {
+        // the sub-histograms summed into the first, two threads per symbol
+        const uint32_t sy = threadIdx.x >> 1;
+        uint32_t c = 0;
+#pragma unroll
+        for (uint32_t rep = 0; rep < kWideReplicas / 2; ++rep)
+          c += hist[(2 * rep + (threadIdx.x & 1)) * kHistStride + sy];
+        c += dpp_mov<0xB1>(c);  // the neighbour's half
+        __syncthreads();
+        if ((threadIdx.x & 1) == 0) hist[sy] = c;
+        __syncthreads();
+      }
+      uint32_t x = kStateLo;
+      if (wave == 0) {
+        if constexpr (SHARED) enc_entries(t, enc);
+        else build_enc_table<false, 1>(hist, n_b, enc, t);
+        for (uint32_t i = lane; i < kStageTail / 4; i += 64) ((uint32_t *)(stage16 + a.wcap))[i] = 0;
+        wave_lds_fence();
+        const uint32_t hd = SHARED ? kSharedSectionFixed : kSectionFixed + 2 * uniform(t.k);
+        const uint32_t limit = (n_b > hd) ? (n_b - hd + 1) / 2 : 0;
+        const uint32_t nw = code_block_lds(syms, enc, n_b, kEncTableBytes + kStageHead, a.wcap, limit,
+                                           (lds16_t *)smem_base + kEncTableBytes / 2 + lane, x);
+        const bool st = nw >= limit;  // (limit 0: always)
+        if (!st) write_section_head<SHARED>(stage, kStageHead + 2 * (a.wcap - nw) - hd, x, t);
+        if (lane == 0) {
+          sh->hdr = hd;
+          sh->words = nw;
+          sh->stored = st;
+        }
+      }
+      __syncthreads();
+      const uint32_t hdr = uniform(sh->hdr), n_words = uniform(sh->words);
+      const bool stored = uniform(sh->stored) != 0;
+      const uint64_t img = hdr + 2ull * n_words;
+      Fin f;
+      f.sout = sout;
+      f.src = src;
+      f.coded_off = g.coded_off;
+      f.dir_end = dir_end;
+      f.chunk_n = chunk_n;
+      f.blk0 = blk0;
+      f.sec_len = stored ? pad16(n_b) : pad16(img);
+      f.img = (uint32_t)img;
+      f.b = b;
+      f.chunk = chunk;
+      f.lb = lb;
+      f.first_block = b - lb;
+      f.n_blocks = g.n_blocks;
+      f.n_b = n_b;
+      f.rounds = rounds;
+      f.A = stored ? 0u : kStageHead + 2 * (a.wcap - n_words) - hdr;
+      f.lds_bytes = (uint32_t)img;
+      f.slot_delta = 0;
+      f.sym_lds = syms;
+      f.stored = stored;
+      f.spilled = false;
+      f.last = lb + 1 == g.n_blocks;
+      finish_wide<DT, SYS>(a, f, stage, sh, wave == 0, 64 * kWideWaves);
+    }
+  }
+  if (wave == 0) finish_launch<SYS, false>(a);
 }
 
 // Compress kernels keep two waves per SIMD (the LDS budget allows eight
@@ -2384,7 +2659,7 @@ struct ReduceArgs {
   uint32_t *dstatus;
   // reduce_fused_kernel: byte offsets of its LDS regions (the decoders'
   // tables and rings, later the coding pass's staging area, start at 0)
-  uint32_t lds_slabs, lds_hist, lds_syms, lds_enc;
+  uint32_t lds_slabs, lds_hist, lds_syms, lds_enc, lds_shared;
 };
 
 uint32_t reduce_lds(int n_in, uint32_t E) { return n_in * (kDecLds + 2 * kRound * E) + kHistBytes; }
@@ -2550,9 +2825,9 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_decode_kernel(
 // input groups), adds the local share, rounds to the element type, writes
 // the output stream's raw plane (and the caller's copy of the reduced
 // tensor), and keeps the block's symbols and histogram in LDS.  After the
-// last round the decoding waves end and the reducing wave codes the block
-// from LDS -- table, the 64 rANS states backwards, words staged where the
-// lookup tables were -- and places its section with the single-pass scan.
+// last round the reducing wave codes the block from LDS (words staged where
+// the lookup tables were) and places its section with the single-pass scan;
+// all waves copy it out.
 // The reduced tensor does not go through HBM.
 // ---------------------------------------------------------------------------
 template <int DT>
@@ -2561,12 +2836,11 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
   constexpr int NW = 4 * (E / 2);
   constexpr uint32_t kSlab = kRound * E;
   extern __shared__ __align__(16) uint8_t smem_base[];
-  __shared__ uint32_t s_block;
-  typedef __attribute__((address_space(3))) uint16_t lds16_t;
   const uint32_t wave = uniform(threadIdx.x >> 6);
   const uint32_t lane = lane_id();
   const int n_in = r.n_in;
-  const bool decoder = (int)wave < n_in;
+  const bool decoder = (int)wave < n_in, reducer = !decoder;
+  WideShared *sh = (WideShared *)(smem_base + r.lds_shared);
   uint8_t *slabs = smem_base + r.lds_slabs;  // [2][n_in][512 elements]
   uint32_t *hist = (uint32_t *)(smem_base + r.lds_hist);
   uint8_t *syms = smem_base + r.lds_syms;    // the block's symbols, 512 per round
@@ -2574,12 +2848,12 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
 
   // the output block: taken in ticket order, so a workgroup only ever waits
   // in the scan for blocks of workgroups that started before it
-  if (!decoder) {
-    if (lane == 0) s_block = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (reducer) {
+    if (lane == 0) sh->block = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     for (uint32_t i = lane; i < kHistReplicas * kHistStride; i += 64) hist[i] = 0;
   }
   __syncthreads();
-  const uint32_t b = uniform(s_block);
+  const uint32_t b = uniform(sh->block);
   if (b >= a.n_blocks) return;  // (the grid has exactly one workgroup per block)
   const uint64_t blk0 = (uint64_t)b * be;
   const uint32_t n_b = (uint32_t)((r.n - blk0) < be ? (r.n - blk0) : be);
@@ -2655,7 +2929,7 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
       if (E == 4) dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
     }
     __syncthreads();
-    if (!decoder && valid > 0) {
+    if (reducer && valid > 0) {
       float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
       if (!r.first) {
 #pragma unroll
@@ -2717,49 +2991,38 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
     if (__any(bad) && lane == 0) report(r.dstatus, UZIP_ECORRUPT);
   }
   __syncthreads();
-  if (decoder) return;
 
-  // ---- the reducing wave codes the block (the decoding waves have ended) ----
+  // ---- the reducing wave codes the block, all waves copy it out ----
   uint4 *enc = (uint4 *)(smem_base + r.lds_enc);
   uint8_t *stage = smem_base;  // where the lookup tables and rings were
-  lds16_t *trash = (lds16_t *)smem_base + lane;  // (the staging area's head)
   uint16_t *stage16 = (uint16_t *)(stage + kStageHead);
-  if (b + 1 == a.n_blocks && lane < 16) {
-    // zero padding after the raw plane (pad16 of (E-1) n bytes)
-    const uint64_t rbyte = g.raw_off + (uint64_t)(E - 1) * r.n + lane;
-    if (rbyte < g.coded_off) a.out[rbyte] = 0;
+  if (reducer) {
+    typedef __attribute__((address_space(3))) uint16_t lds16_t;
+    if (b + 1 == a.n_blocks && lane < 16) {
+      // zero padding after the raw plane (pad16 of (E-1) n bytes)
+      const uint64_t rbyte = g.raw_off + (uint64_t)(E - 1) * r.n + lane;
+      if (rbyte < g.coded_off) a.out[rbyte] = 0;
+    }
+    Table t;
+    build_enc_table(hist, n_b, enc, t);
+    for (uint32_t i = lane; i < kStageTail / 4; i += 64) ((uint32_t *)(stage16 + a.wcap))[i] = 0;
+    wave_lds_fence();
+    const uint32_t hd = kSectionFixed + 2 * uniform(t.k);
+    const uint32_t limit = (n_b > hd) ? (n_b - hd + 1) / 2 : 0;
+    uint32_t x = kStateLo;
+    const uint32_t nw = code_block_lds(syms, enc, n_b, (uint32_t)(uintptr_t)(lds16_t *)smem_base + kStageHead, a.wcap,
+                                       limit, (lds16_t *)smem_base + lane, x);
+    const bool st = nw >= limit;  // (limit 0: always)
+    if (!st) write_section_head<false>(stage, kStageHead + 2 * (a.wcap - nw) - hd, x, t);
+    if (lane == 0) {
+      sh->hdr = hd;
+      sh->words = nw;
+      sh->stored = st;
+    }
   }
-  wave_lds_fence();
-  Table t;
-  build_enc_table(hist, n_b, enc, t);
-  t.k = uniform(t.k);
-  wave_lds_fence();
-  const uint32_t hdr = kSectionFixed + 2 * t.k;
-  for (uint32_t i = lane; i < kStageTail / 4; i += 64) ((uint32_t *)(stage16 + a.wcap))[i] = 0;
-  const uint32_t limit_words = (n_b > hdr) ? (n_b - hdr + 1) / 2 : 0;
-  uint32_t pos = a.wcap;  // staging indices [pos, wcap) hold the words so far; the block's words all fit
-  const uint32_t rel = (uint32_t)(uintptr_t)(lds16_t *)smem_base + kStageHead;
-  uint32_t xs = kStateLo;
-  bool stored = (limit_words == 0);
-  if (full < rounds && !stored) {  // the partial last round comes first
-    const uint32_t i0 = full * kRound + kPerLane * lane;
-    const uint32_t valid = i0 < n_b ? (n_b - i0 < 8 ? n_b - i0 : 8) : 0;
-    const uint2 sv = *(const uint2 *)(syms + full * kRound + kPerLane * lane);
-    const uint32_t sy[2] = {sv.x, sv.y};
-    uint4 e[8];
-    enc_lookup8(enc, sy[0], sy[1], e);
-    enc_round<false>(xs, e, valid, pos, rel, trash);
-    if (a.wcap - pos >= limit_words) stored = true;
-  }
-  for (int q2 = (int)full - 1; q2 >= 0 && !stored; --q2) {
-    const uint2 sv = *(const uint2 *)(syms + (uint32_t)q2 * kRound + kPerLane * lane);
-    uint4 e[8];
-    enc_lookup8(enc, sv.x, sv.y, e);
-    enc_round<true>(xs, e, 8, pos, rel, trash);
-    if (a.wcap - pos >= limit_words) stored = true;
-  }
-  pos = uniform(pos);
-  const uint32_t n_words = a.wcap - pos;
+  __syncthreads();
+  const uint32_t hdr = uniform(sh->hdr), n_words = uniform(sh->words);
+  const bool stored = uniform(sh->stored) != 0;
   const uint64_t img = hdr + 2ull * n_words;
   const uint64_t sec_len = stored ? pad16(n_b) : pad16(img);
   Fin f;
@@ -2778,18 +3041,15 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_fused_kernel(R
   f.n_blocks = g.n_blocks;
   f.n_b = n_b;
   f.rounds = rounds;
-  f.A = kStageHead + 2 * pos - hdr;
+  f.A = stored ? 0u : kStageHead + 2 * (a.wcap - n_words) - hdr;
   f.lds_bytes = (uint32_t)img;
   f.slot_delta = 0;
   f.sym_lds = syms;
   f.stored = stored;
   f.spilled = false;
   f.last = b + 1 == a.n_blocks;
-  if (!stored) write_section_head<false>(stage, f.A, xs, t);
-  wave_lds_fence();
-  publish_aggregate(a.status, b, 0, sec_len / 16, a.ticket[kWsHold]);
-  finish_block<DT, false>(a, f, stage, nullptr);
-  finish_launch<false, true>(a);
+  finish_wide<DT, false>(a, f, stage, sh, reducer, blockDim.x);
+  if (reducer) finish_launch<false, true>(a);
 }
 
 // zero the ticket, the look-back status words and the chunk counters
@@ -3032,6 +3292,22 @@ const void *shared_kernel_ptr(int k) {
       (const void *)encode_kernel<4, false, true, true>,  (const void *)encode_kernel<4, true, true, true>};
   return tab[k];
 }
+// wide encoders: index = dt * 4 + 2 * (write-through stores) + (stream-wide table)
+constexpr int kWideKernels = 20;
+const void *wide_kernel_ptr(int k) {
+  static const void *const tab[kWideKernels] = {
+      (const void *)encode_wide_kernel<0, false, false>, (const void *)encode_wide_kernel<0, false, true>,
+      (const void *)encode_wide_kernel<0, true, false>,  (const void *)encode_wide_kernel<0, true, true>,
+      (const void *)encode_wide_kernel<1, false, false>, (const void *)encode_wide_kernel<1, false, true>,
+      (const void *)encode_wide_kernel<1, true, false>,  (const void *)encode_wide_kernel<1, true, true>,
+      (const void *)encode_wide_kernel<2, false, false>, (const void *)encode_wide_kernel<2, false, true>,
+      (const void *)encode_wide_kernel<2, true, false>,  (const void *)encode_wide_kernel<2, true, true>,
+      (const void *)encode_wide_kernel<3, false, false>, (const void *)encode_wide_kernel<3, false, true>,
+      (const void *)encode_wide_kernel<3, true, false>,  (const void *)encode_wide_kernel<3, true, true>,
+      (const void *)encode_wide_kernel<4, false, false>, (const void *)encode_wide_kernel<4, false, true>,
+      (const void *)encode_wide_kernel<4, true, false>,  (const void *)encode_wide_kernel<4, true, true>};
+  return tab[k];
+}
 const void *reduce_kernel_ptr(int dt) {
   static const void *const tab[3] = {(const void *)reduce_kernel<0>, (const void *)reduce_kernel<1>,
                                      (const void *)reduce_kernel<2>};
@@ -3075,6 +3351,8 @@ uzip_status device_info(DeviceInfo &out) {
       (void)hipFuncSetAttribute(encode_kernel_ptr(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
     for (int k = 0; k < kSharedKernels; ++k)
       (void)hipFuncSetAttribute(shared_kernel_ptr(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
+    for (int k = 0; k < kWideKernels; ++k)
+      (void)hipFuncSetAttribute(wide_kernel_ptr(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
     for (int k = 0; k < 3; ++k)
       (void)hipFuncSetAttribute(reduce_kernel_ptr(k), hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
     bool at0 = true;
@@ -3089,10 +3367,9 @@ uzip_status device_info(DeviceInfo &out) {
     (void)hipFuncSetAttribute((const void *)reduce_decode_kernel<0>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
     (void)hipFuncSetAttribute((const void *)reduce_decode_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
     (void)hipFuncSetAttribute((const void *)reduce_decode_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
-    // (reduce_fused_kernel has a few bytes of static LDS besides)
-    (void)hipFuncSetAttribute((const void *)reduce_fused_kernel<0>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max - 1024);
-    (void)hipFuncSetAttribute((const void *)reduce_fused_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max - 1024);
-    (void)hipFuncSetAttribute((const void *)reduce_fused_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max - 1024);
+    (void)hipFuncSetAttribute((const void *)reduce_fused_kernel<0>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
+    (void)hipFuncSetAttribute((const void *)reduce_fused_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
+    (void)hipFuncSetAttribute((const void *)reduce_fused_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
     (void)hipFuncSetAttribute((const void *)table_kernel<0>, hipFuncAttributeMaxDynamicSharedMemorySize, kTableLds);
     (void)hipFuncSetAttribute((const void *)table_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, kTableLds);
     (void)hipFuncSetAttribute((const void *)table_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, kTableLds);
@@ -3157,6 +3434,27 @@ uint32_t encode_lds(uint32_t block_elems) {
   return kEncTableBytes + (pass1 > pass2 ? pass1 : pass2);
 }
 
+// LDS bytes of encode_wide_kernel: the encoder table, the staging area of a
+// whole block's words (before, the histogram), the symbols and what the
+// workgroup shares
+uint32_t wide_syms_off(uint32_t block_elems) {
+  const uint32_t stage = (uint32_t)pad16(kStageHead + 2 * word_cap(block_elems) + kStageTail);
+  return kEncTableBytes + (stage > kWideHist ? stage : kWideHist);
+}
+uint32_t wide_lds(uint32_t block_elems) {
+  return wide_syms_off(block_elems) + (block_elems + kRound - 1) / kRound * kRound + (uint32_t)pad16(sizeof(WideShared));
+}
+// Workgroups of it that a compute unit takes at once: as many as its LDS
+// holds, up to two.  64 KiB bf16 blocks, one wave per block against a
+// workgroup: 4 blocks 45.4 -> 35.6 us, 256 blocks 50.3 -> 42.7, 512 blocks
+// 59.2 -> 56.2; 16 KiB blocks, 367: 31.1 -> 25.1, 4 KiB blocks, 293: 25.1 ->
+// 18.5.  With four on a compute unit their first passes and copy-outs only
+// take turns: 977 blocks of 32 KiB 60.9 -> 69.0, of 16 KiB 52.5 -> 52.8.
+uint32_t wide_per_cu(uint32_t block_elems) {
+  const uint32_t k = 160 * 1024 / wide_lds(block_elems);
+  return k < 2 ? k : 2;
+}
+
 struct EncodeWs {
   uint64_t status_off, cnt_off, slot_off, y_off, total;
   uint64_t slots;  // overflow slots: the persistent grid's upper bound
@@ -3196,12 +3494,13 @@ ReduceWs reduce_ws(uint64_t n_blocks, uint32_t block_elems, uint64_t n, uint32_t
 
 // LDS of reduce_fused_kernel for n_in decoding waves: the decoders' tables
 // and rings (or, once they are done, the staging area of a whole block's
-// words), the slabs, the histogram, the block's symbols, the encoder table
-// and the trash slots; 0 if the block does not fit (larger blocks take the
-// decode-reduce kernel and the encoder's coding pass instead).
+// words), the slabs (then the encoder table), the histogram, the block's
+// symbols and what the workgroup shares; 0 if the block does not fit (larger
+// blocks take the decode-reduce kernel and the encoder's coding pass
+// instead).
 constexpr uint32_t kLdsMax = 160 * 1024;
 uint32_t fused_layout(int n_in, uint32_t E, uint32_t block_elems, ReduceArgs *r) {
-  const uint32_t stage = kStageHead + 2 * word_cap(block_elems) + kStageTail;
+  const uint32_t stage = (uint32_t)pad16(kStageHead + 2 * word_cap(block_elems) + kStageTail);
   const uint32_t dec = (uint32_t)n_in * kDecLds;
   uint32_t o = (dec > stage ? dec : stage);
   o = (o + 15u) & ~15u;
@@ -3212,13 +3511,16 @@ uint32_t fused_layout(int n_in, uint32_t E, uint32_t block_elems, ReduceArgs *r)
   const uint32_t hist = o;
   o += kHistBytes;
   const uint32_t syms = o;
-  o += (block_elems + 15u) & ~15u;
-  if (o + 1024 > kLdsMax) return 0;  // (the kernel's own static bytes besides)
+  o += (block_elems + kRound - 1) / kRound * kRound;
+  const uint32_t shared = o;
+  o += (uint32_t)sizeof(WideShared);
+  if (o > kLdsMax) return 0;
   if (r != nullptr) {
     r->lds_slabs = slabs;
     r->lds_hist = hist;
     r->lds_syms = syms;
     r->lds_enc = enc;
+    r->lds_shared = shared;
   }
   return o;
 }
@@ -3277,19 +3579,24 @@ uzip_status launch_encode(EncodeArgs &a, uzip_dtype dt, bool reduce, uint8_t *ws
   const uint64_t chunks = ((uint64_t)a.n_blocks + a.blocks_per_chunk - 1) / a.blocks_per_chunk;
   const uint64_t most = a.n_blocks < w.slots ? a.n_blocks : w.slots;
   const bool even = chunks >= 8 * kMaxXcd || (chunks >= kMaxXcd && chunks % kMaxXcd == 0);
-  a.n_xcd = (!reduce && a.flags != nullptr && info.cus == 32 * (int)kMaxXcd && even && most >= (uint64_t)info.cus)
+  // a workgroup per block while all of them are resident at once
+  const bool wide = small && a.n_blocks <= (uint64_t)info.cus * wide_per_cu(a.block_elems);
+  a.n_xcd = (!reduce && !wide && a.flags != nullptr && info.cus == 32 * (int)kMaxXcd && even && most >= (uint64_t)info.cus)
                 ? kMaxXcd
                 : 0;
   const int kind = (a.flags != nullptr && a.n_xcd == 0 ? 2 : 0) + (small ? 1 : 0);
   const void *fn = reduce   ? reduce_kernel_ptr((int)dt)
                    : shared ? shared_kernel_ptr((int)dt * 4 + kind)
                             : encode_kernel_ptr((int)dt * 4 + kind);
-  int occ = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, 64, lds) != hipSuccess || occ < 1) occ = 1;
-  uint64_t grid = (uint64_t)info.cus * (uint64_t)occ;
-  if (grid > a.n_blocks) grid = a.n_blocks;
-  if (grid > w.slots) grid = w.slots;
-  if (grid == 0) grid = 1;
+  uint64_t grid = a.n_blocks;
+  if (!wide) {
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, 64, lds) != hipSuccess || occ < 1) occ = 1;
+    grid = (uint64_t)info.cus * (uint64_t)occ;
+    if (grid > a.n_blocks) grid = a.n_blocks;
+    if (grid > w.slots) grid = w.slots;
+    if (grid == 0) grid = 1;
+  }
   const uint64_t clear_words = w.slot_off / 4;
   const uint64_t cgrid = (clear_words + 255) / 256 < 4096 ? (clear_words + 255) / 256 : 4096;
   hipLaunchKernelGGL(clear_kernel, dim3((unsigned)cgrid), dim3(256), 0, stream, (uint32_t *)ws, clear_words,
@@ -3297,6 +3604,14 @@ uzip_status launch_encode(EncodeArgs &a, uzip_dtype dt, bool reduce, uint8_t *ws
                      (uint64_t)(uintptr_t)dstatus);
   if (hipGetLastError() != hipSuccess) return UZIP_EHIP;
   void *args[] = {&a};
+  if (wide) {
+    a.pass2_off = wide_syms_off(a.block_elems);
+    const void *wfn = wide_kernel_ptr((int)dt * 4 + (a.flags != nullptr ? 2 : 0) + (shared ? 1 : 0));
+    if (hipLaunchKernel(wfn, dim3((unsigned)grid), dim3(64 * kWideWaves), args, wide_lds(a.block_elems), stream) !=
+        hipSuccess)
+      return UZIP_EHIP;
+    return UZIP_OK;
+  }
   if (hipLaunchKernel(fn, dim3((unsigned)grid), dim3(64), args, lds, stream) != hipSuccess) return UZIP_EHIP;
   return UZIP_OK;
 }

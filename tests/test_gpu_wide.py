@@ -1,0 +1,108 @@
+"""GPU: calls of few blocks, coded by a workgroup per block, and the line to
+the encoder of one wave per block (512 blocks on a chip of 256 compute
+units), against the oracle byte for byte.
+
+The other encoder tests use small tensors, which the workgroup encoder
+takes; the cases past the line here are what holds the one-wave encoder to
+the same edges: staging windows that slide, STORED blocks, partial last
+blocks, the XCD-local producer."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ref
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+EB = {"bf16": 2, "fp16": 2, "fp32": 4, "e4m3fn": 2, "e5m2": 2}
+LINE = 512
+
+
+@pytest.fixture(scope="module")
+def uz():
+    import paper_2604_17172_amd as m
+    return m
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a).view(np.int16 if a.itemsize == 2 else np.int32)).cuda()
+
+
+def values(dtype, n, seed):
+    """Ordinary values with stretches of random bits (STORED blocks) and of
+    one value (a table of one symbol)."""
+    if dtype in ("e4m3fn", "e5m2"):
+        x = W.normal_fp8_pairs(n, dtype, seed=seed)
+    elif dtype == "bf16":
+        x = W.normal_bf16(n, seed=seed)
+    elif dtype == "fp16":
+        x = W.grad_fp16(n, seed=seed)
+    else:
+        x = W.grad_fp32(n, seed=seed)
+    rng = np.random.Generator(np.random.PCG64(seed))
+    for _ in range(3):
+        a, m = int(rng.integers(0, n)), int(rng.integers(1, n // 6 + 2))
+        x[a:a + m] = rng.integers(0, 1 << (8 * x.itemsize), x[a:a + m].size, dtype=np.uint64).astype(x.dtype)
+        a = int(rng.integers(0, n))
+        x[a:a + m] = x[a]
+    return x
+
+
+def check(uz, x, dtype, bb):
+    xt = dev(x)
+    out, size = uz.compress(xt, bb, dtype=dtype, check=True)
+    assert np.array_equal(out[: int(size.item())].cpu().numpy(), ref.compress(x, dtype, bb)), (dtype, bb, x.size)
+    out, size = uz.compress_table(xt, bb, "sampled", dtype=dtype)
+    torch.cuda.synchronize()
+    assert np.array_equal(out[: int(size.item())].cpu().numpy(), ref.compress_table(x, dtype, bb, "sampled")), \
+        (dtype, bb, x.size, "sampled")
+
+
+def check_chunks(uz, x, dtype, bb, cb):
+    for mode in ("per_block", "sampled"):
+        out, slot, sizes, flags = uz.compress_chunked_table(dev(x), bb, cb, mode, dtype=dtype, epoch=3)
+        torch.cuda.synchronize()
+        assert bool((flags == 3).all())
+        buf, sz = out.cpu().numpy(), sizes.cpu().numpy()
+        for c, want in enumerate(ref.compress_chunked(x, dtype, bb, cb, mode)):
+            assert np.array_equal(buf[c * slot:c * slot + sz[c]], want), (dtype, bb, cb, x.size, mode, c)
+
+
+# elements of the last block: the rounds' (512), the waves' (8 rounds) and the
+# largest block's edges
+@pytest.mark.parametrize("tail", [1, 511, 513, 8 * 512 - 1, 8 * 512 + 1, 9 * 512, 63 * 512 + 7, 64 * 512 - 1])
+@pytest.mark.parametrize("dtype", sorted(EB))
+def test_block_edges(uz, dtype, tail):
+    bb = 32768 * EB[dtype]
+    check(uz, values(dtype, tail, seed=tail), dtype, bb)
+    check(uz, values(dtype, 2 * 32768 + tail, seed=tail), dtype, bb)
+    check_chunks(uz, values(dtype, 3 * 32768 + tail, seed=tail), dtype, bb, 2 * bb)
+
+
+@pytest.mark.parametrize("blocks", [LINE - 1, LINE, LINE + 1])
+@pytest.mark.parametrize("dtype", sorted(EB))
+def test_blocks_around_the_line(uz, dtype, blocks):
+    be = 4096 // EB[dtype]
+    x = values(dtype, (blocks - 1) * be + be // 3, seed=blocks)
+    check(uz, x, dtype, 4096)
+    # 16 KiB chunks: past 64 chunks (and 512 blocks) coded XCD by XCD
+    check_chunks(uz, x, dtype, 4096, 16384)
+    check_chunks(uz, x, dtype, 4096, 4096 * 100)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16", "fp32", "e4m3fn"])
+def test_one_wave_per_block_spills_and_stores(uz, dtype):
+    """Past the line in the largest blocks that keep their symbols in
+    registers: words beyond the staging window, STORED blocks."""
+    be = 32768
+    n = (LINE + 3) * be + 777
+    x = np.tile(values(dtype, 37 * be + 11, seed=5), n // (37 * be) + 1)[:n].copy()
+    if dtype in ("bf16", "fp16"):
+        # exponents spread until a block needs more than the window holds
+        rng = np.random.Generator(np.random.PCG64(9))
+        m = 40 * be
+        e = rng.integers(95, 159, m) << 7 if dtype == "bf16" else rng.integers(1, 31, m) << 10
+        low = rng.integers(0, 1 << (7 if dtype == "bf16" else 10), m)
+        x[: m] = (e | low | rng.integers(0, 2, m) << 15).astype(x.dtype)
+    check(uz, x, dtype, be * EB[dtype])
