@@ -22,10 +22,14 @@
 //                   of up to 32768 elements resolve their offset and write
 //                   their section only after the wave's next block has
 //                   streamed through pass 1.
+//   encode_wide_kernel  the same for few blocks: a workgroup of eight waves
+//                   per block shares pass 1 and the copy-out.
 //   decode_kernel   resident waves walk the blocks grid-stride; each block's
 //                   offset is read from the directory, its decode table
-//                   (2048 x u32) is built in LDS, its words are staged
-//                   through an LDS ring and the 64 states decode forwards.
+//                   (2048 x u32) is built in LDS, its words enter an LDS
+//                   ring with their table entries and the 64 states decode
+//                   forwards.  decode_wide_kernel: two waves per block, for
+//                   few blocks.
 //                   For the receiver of the split-send producer the walk
 //                   covers the blocks of a range of chunk streams at once,
 //                   opening each chunk's header when it reaches that chunk.
@@ -131,6 +135,9 @@ struct DecodeArgs {
   uint64_t n_chunks;
   uint32_t bpc;
   uint32_t block_elems;
+  // one stream: this launch decodes it if it has [min_blocks, max_blocks]
+  // blocks, or (min_blocks > max_blocks) if it has not those between
+  uint64_t min_blocks, max_blocks;
 };
 
 // first error wins
@@ -409,14 +416,15 @@ __device__ void fill_lut(const uint32_t f[4], uint32_t *lut) {
 }
 
 // Lookup table of a stream-wide table (u16 f[256] in memory): every symbol
-// has f >= 1 and the sum is M, else false (uniformly).
-__device__ bool build_lut_shared(const uint16_t *table, uint32_t *lut) {
+// has f >= 1 and the sum is M, else false (uniformly).  `fill`: this wave
+// writes it.
+__device__ bool build_lut_shared(const uint16_t *table, uint32_t *lut, bool fill) {
   const uint32_t lane = lane_id();
   const uint2 v = *(const uint2 *)(table + 4 * lane);
   const uint32_t f[4] = {v.x & 0xFFFFu, v.x >> 16, v.y & 0xFFFFu, v.y >> 16};
   const bool bad = f[0] == 0 || f[1] == 0 || f[2] == 0 || f[3] == 0;
   if (__any(bad) || wave_sum(f[0] + f[1] + f[2] + f[3]) != kM) return false;
-  fill_lut(f, lut);
+  if (fill) fill_lut(f, lut);
   return true;
 }
 
@@ -2018,8 +2026,10 @@ __global__ void __launch_bounds__(64) reduce_kernel(EncodeArgs a) {
 // e and r of its slot w & 2047.
 // Measured (interleaved A/B against the two-read chain with a ring of plain
 // words): 171 cycles a sub-step on a lone wave, 256 KiB of bf16 53.9 -> 40.3
-// us, 214 MB of fp32 119 -> 95 us, the 1 GiB weight buffer 404 -> 391 us (3
-// waves a SIMD instead of 4: it is held by memory, 4.57 TB/s).  A lone wave
+// us, 214 MB of fp32 119 -> 95 us, the 1 GiB weight buffer 404 -> 390 us (3
+// waves a SIMD instead of 4: it is held by memory, 4.57 TB/s).  fp32 in
+// 64 KiB blocks is the one type that loses where its blocks fit one pass
+// (1633 blocks 41.7 -> 43.6 us; 6104 blocks 181 -> 173).  A lone wave
 // issues an instruction in ~5 cycles whatever it depends on, so what is left
 // of the chain is its ~26 instructions.
 //
@@ -2075,7 +2085,7 @@ __device__ __forceinline__ bool dec_at_start(const DecState &d, const uint32_t *
 // lane without an element).  Branch-free: every lane reads the table at its
 // new state's slot and the ring at its would-be word; positions past the
 // section's words stay inside the ring and are caught once per block.
-template <bool FULL, typename F>
+template <bool FULL, uint32_t RW = kRingWords, typename F>
 __device__ __forceinline__ uint32_t decode_step(DecState &d, bool valid, const uint32_t *lut, const uint8_t *ring,
                                                 uint32_t &q, F fill) {
   typedef uint32_t v2u __attribute__((ext_vector_type(2)));
@@ -2086,14 +2096,16 @@ __device__ __forceinline__ uint32_t decode_step(DecState &d, bool valid, const u
   const bool need = (FULL || valid) && x < kStateLo;
   const uint64_t m = __ballot(need);
   const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-  const uint32_t rb = q & (8 * kRingWords - 1);
+  const uint32_t rb = q & (8 * RW - 1);
   const v2u v = *(const volatile __attribute__((address_space(3))) v2u *)((const lds8_t *)ring + (rb + 8 * rank));
   __builtin_amdgcn_sched_barrier(0);
   // (the compiler would keep a sum of the counts besides)
   q = uniform(q);
   asm("s_lshl3_add_u32 %0, %1, %0" : "+s"(q) : "s"((uint32_t)__popcll(m)) : "scc");
-  const uint32_t t = need ? x << 5 : x >> kProbBits;
+  uint32_t t = need ? x << 5 : x >> kProbBits;
+  asm volatile("" : "+v"(t));  // (here, not after the reads)
   fill();
+  __builtin_amdgcn_sched_barrier(0);
   const uint32_t ef = el & kEntryMask, er = (el >> 12) & 0x7FFu;
   __builtin_amdgcn_sched_barrier(0);
   const uint32_t e = need ? v.x : ef;
@@ -2104,11 +2116,12 @@ __device__ __forceinline__ uint32_t decode_step(DecState &d, bool valid, const u
   return (FULL || valid) ? used : 0u;
 }
 
-// A chunk's 4 words of this lane into the ring at word `slot` (0 or 256).
+// A chunk's 4 words of this lane into the ring at word `slot`.
 __device__ __forceinline__ uint2 ring_entry(const uint32_t *lut, uint32_t w) {
   const uint32_t e = lut[w & (kM - 1)];
   return make_uint2(e & kEntryMask, __umul24(e & 0xFFFu, w >> kProbBits) + ((e >> 12) & 0x7FFu));
 }
+template <uint32_t RW = kRingWords>
 __device__ __forceinline__ void ring_put(uint8_t *ring, const uint32_t *lut, uint32_t slot, uint2 v) {
   const uint32_t lane = lane_id();
   const uint2 e0 = ring_entry(lut, v.x & 0xFFFFu), e1 = ring_entry(lut, v.x >> 16);
@@ -2118,7 +2131,7 @@ __device__ __forceinline__ void ring_put(uint8_t *ring, const uint32_t *lut, uin
   d[0] = a;
   d[1] = b;
   if (slot == 0 && lane < kRingMirror / 4) {
-    uint4 *dm = (uint4 *)(ring + 8 * kRingWords + 32 * lane);
+    uint4 *dm = (uint4 *)(ring + 8 * RW + 32 * lane);
     dm[0] = a;
     dm[1] = b;
   }
@@ -2301,6 +2314,63 @@ __device__ uint32_t open_input_block(const uint8_t *s, uint64_t in_bytes, uint64
   return kCoded;
 }
 
+// ---------------------------------------------------------------------------
+// The dense decoder's ring: plain words, 2 KB without a mirror (8 KB table +
+// 2 KB ring = 10 KB of LDS per wave, 16 waves per compute unit where the ring
+// of entries allows 12), 512-byte chunks read with one 8-byte load per lane.
+// A half round (4 sub-steps) reads at most 512 bytes; each half round stores
+// the chunk its slot fetched a round earlier and fetches the next chunk if it
+// will fit when stored (front < cur + 1536), else re-fetches the newest
+// chunk.  Two slots alternate by half round.  The stored frontier then stays
+// at least 512 bytes ahead of the words a half round reads, and a store never
+// overwrites unread words.  A sub-step waits for two LDS reads, one after the
+// other: this form only pays where its 16 waves take all blocks at once and
+// 12 would not (4096 blocks of 64 KiB: 89 us against 100).
+// ---------------------------------------------------------------------------
+constexpr uint32_t kDecRingBytes = 2048;
+constexpr uint32_t kDecChunk = 512;
+
+template <bool FULL>
+__device__ __forceinline__ uint32_t decode_step_ring(uint32_t &x, bool valid, const uint32_t *lut,
+                                                     const uint8_t *ring, uint32_t &rb, uint32_t &p) {
+  uint32_t e = 0;
+  if (FULL || valid) {
+    e = lut[x & (kM - 1)];
+    x = __umul24(e & 0xFFFu, x >> kProbBits) + ((e >> 12) & 0x7FFu);
+  }
+  const bool need = (FULL || valid) && x < kStateLo;
+  const uint64_t m = __ballot(need);
+  const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+  uint32_t w = *(const uint16_t *)(ring + ((rb + 2 * rank) & (kDecRingBytes - 1)));
+  asm volatile("" : "+v"(w));  // keep the read unconditional: no exec-mask branch around it
+  x = need ? ((x << 16) | w) : x;
+  const uint32_t c = (uint32_t)__popcll(m);
+  p += c;
+  rb = (rb + 2 * c) & (kDecRingBytes - 1);
+  // the ring offset stays a scalar of its own: the compiler would rebuild it
+  // from p with one more vector add per sub-step
+  rb = __builtin_amdgcn_readfirstlane(rb);
+  return e;
+}
+
+struct RingD {
+  uint32_t len;
+  uint32_t front;
+  uint32_t pos[2];
+  uint2 pv[2];
+};
+
+template <int X>
+__device__ __forceinline__ void ringd_half(RingD &rg, uint8_t *ring, const uint8_t *sec, uint32_t cur) {
+  const uint32_t lane = lane_id();
+  *(uint2 *)(ring + ((rg.pos[X] + 8 * lane) & (kDecRingBytes - 1))) = rg.pv[X];
+  asm volatile("" ::: "memory");  // the ring stores stay before the half round's ring reads
+  rg.front += rg.front < cur + 3 * kDecChunk ? kDecChunk : 0;
+  rg.pos[X] = rg.front - kDecChunk;
+  const uint32_t o = rg.pos[X] + 8 * lane;
+  rg.pv[X] = *(const uint2 *)(sec + (o + 8 <= rg.len ? o : rg.len - 8));
+}
+
 template <int E>
 __device__ inline void load_raw_full(const uint8_t *plane, uint64_t first, uint32_t raw[6]) {
   const uint2 *q = (const uint2 *)(plane + (uint64_t)(E - 1) * first);
@@ -2329,7 +2399,8 @@ struct DecStream {
 // bits, flags | block elements | blocks | elements (2) | total bytes (2))
 // and sets up its geometry; builds the stream-wide lookup table.
 template <int DT, bool SHARED>
-__device__ bool open_stream(const DecodeArgs &a, uint64_t c, const Hdr &hv, DecStream &st, uint32_t *lut) {
+__device__ bool open_stream(const DecodeArgs &a, uint64_t c, const Hdr &hv, DecStream &st, uint32_t *lut,
+                            bool fill = true) {
   const Hdr h = uniform_hdr(hv);
   constexpr int E = (DT == 2) ? 4 : 2;
   const bool chunked = a.bpc != 0;
@@ -2364,7 +2435,7 @@ __device__ bool open_stream(const DecodeArgs &a, uint64_t c, const Hdr &hv, DecS
   ok = ok && total >= g.coded_off;
   if (SHARED && ok && nb > 0) {
     // one lookup table for every block of the stream
-    ok = build_lut_shared(mode == 1 ? (const uint16_t *)(s + table_off) : a.table, lut);
+    ok = build_lut_shared(mode == 1 ? (const uint16_t *)(s + table_off) : a.table, lut, fill);
     __syncthreads();
   }
   st.be = be;
@@ -2380,12 +2451,13 @@ __device__ inline bool stream_end_ok(const DecStream &st) {
   return st.g.coded_off + endall == st.total;
 }
 
-template <int DT, bool SHARED = false>
-__global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
+// DENSE: the ring of plain words.
+template <int DT, bool SHARED = false, bool DENSE = false>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DENSE ? 4 : 1))) decode_kernel(DecodeArgs a) {
   constexpr int E = (DT == 2) ? 4 : 2;
   constexpr int NW = 4 * (E / 2);
   __shared__ uint32_t lut[kM];
-  __shared__ __align__(16) uint8_t ring[kRingBytes];
+  __shared__ __align__(16) uint8_t ring[DENSE ? kDecRingBytes : kRingBytes];
   const uint32_t lane = lane_id();
   DecStream st;
   uint64_t cur = 0, n_work = 0;
@@ -2401,6 +2473,10 @@ __global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
     }
     if (blockIdx.x == 0 && lane == 0 && !stream_end_ok(st)) report(a.dstatus, UZIP_ECORRUPT);
     n_work = st.nb;
+    // two launches share a stream whose block count the host does not know:
+    // one of them takes it
+    const bool ge = n_work >= a.min_blocks, le = n_work <= a.max_blocks;
+    if (!(a.min_blocks <= a.max_blocks ? ge && le : ge || le)) return;
   } else {
     // chunk streams: a header is opened when the walk reaches its chunk
     cur = ~0ull;
@@ -2533,49 +2609,132 @@ __global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
     const uint32_t x0 = x;  // checked at the end of the block: no wait for it here
     const uint32_t wb = SHARED ? kSharedSectionFixed : kSectionFixed + 2 * k;  // section offset of word 0
     const uint32_t w_avail = (len - wb) / 2;
-    WordRing rg;
-    ring_open(rg, ring, lut, sec, len, wb, P0, pre0, pre1);
-    __syncthreads();
-    DecState ds = dec_state(x, lut);
-    const uint32_t full = n_b / kRound;
-    uint8_t *outp = st.out + blk0 * E;
-    const uint8_t *rawp = raw_plane + blk0 * (E - 1);
-    // Full rounds, four per iteration.  A round decodes its symbols and, in
-    // the shadow of its LDS reads, merges and stores the round before; its
-    // raw bytes are loaded two rounds ahead of its own decoding, three ahead
-    // of their use (four buffers, no register is copied).
-    uint32_t r = 0;
-    uint32_t raw0[6], raw1[6], raw2[6], raw3[6], ea[kPerLane], eb[kPerLane];
+    if constexpr (!DENSE) {
+      WordRing rg;
+      ring_open(rg, ring, lut, sec, len, wb, P0, pre0, pre1);
+      __syncthreads();
+      DecState ds = dec_state(x, lut);
+      const uint32_t full = n_b / kRound;
+      uint8_t *outp = st.out + blk0 * E;
+      const uint8_t *rawp = raw_plane + blk0 * (E - 1);
+      // Full rounds, four per iteration.  A round decodes its symbols and, in
+      // the shadow of its LDS reads, merges and stores the round before; its
+      // raw bytes are loaded two rounds ahead of its own decoding, three ahead
+      // of their use (four buffers, no register is copied).
+      uint32_t r = 0;
+      uint32_t raw0[6], raw1[6], raw2[6], raw3[6], ea[kPerLane], eb[kPerLane];
 #pragma unroll
-    for (int q = 0; q < (int)kPerLane; ++q) ea[q] = eb[q] = 0;
+      for (int q = 0; q < (int)kPerLane; ++q) ea[q] = eb[q] = 0;
 #pragma unroll
-    for (int q = 0; q < 6; ++q) raw0[q] = raw1[q] = raw2[q] = raw3[q] = 0;
-    auto round = [&](uint32_t rr, uint32_t (&e)[kPerLane], const uint32_t (&ep)[kPerLane],
-                     const uint32_t (&rawp_)[6], uint32_t (&rawn)[6], bool prev) {
-      uint32_t w[NW];
-      ring_land(rg);
-      load_raw_full<E>(rawp, (rr + 2 < full ? rr + 2 : full - 1) * kRound + kPerLane * lane, rawn);
+      for (int q = 0; q < 6; ++q) raw0[q] = raw1[q] = raw2[q] = raw3[q] = 0;
+      auto round = [&](uint32_t rr, uint32_t (&e)[kPerLane], const uint32_t (&ep)[kPerLane],
+                       const uint32_t (&rawp_)[6], uint32_t (&rawn)[6], bool prev) {
+        uint32_t w[NW];
+        ring_land(rg);
+        load_raw_full<E>(rawp, (rr + 2 < full ? rr + 2 : full - 1) * kRound + kPerLane * lane, rawn);
 #pragma unroll
-      for (uint32_t t = 0; t < kPerLane; ++t) {
-        if (t % (kPerLane / 2) == 0) ring_fill(rg, ring, lut);
-        e[t] = decode_step<true>(ds, true, lut, ring, rg.q, [&]() {
-          if (t < 4) {
-            merge_quarter<DT>((int)t, ep, rawp_, w);
-            // (here, not sunk to the store)
-            if constexpr (DT <= 1) {
-              asm volatile("" : "+v"(w[t]));
-            } else if (t & 1) {
+        for (uint32_t t = 0; t < kPerLane; ++t) {
+          if (t % (kPerLane / 2) == 0) ring_fill(rg, ring, lut);
+          e[t] = decode_step<true>(ds, true, lut, ring, rg.q, [&]() {
+            if (t < 4) {
+              merge_quarter<DT>((int)t, ep, rawp_, w);
+              // (here, not sunk to the store)
+              if constexpr (DT <= 1) {
+                asm volatile("" : "+v"(w[t]));
+              } else if (t & 1) {
 #pragma unroll
-              for (int q = 0; q < NW / 2; ++q) asm volatile("" : "+v"(w[NW / 2 * (t >> 1) + q]));
+                for (int q = 0; q < NW / 2; ++q) asm volatile("" : "+v"(w[NW / 2 * (t >> 1) + q]));
+              }
+            }
+            if (t == 4 && prev) store_words<E, true>(outp, (rr - 1) * kRound + kPerLane * lane, 8, w);
+          });
+        }
+      };
+      if (full >= 4) {
+        load_raw_full<E>(rawp, kPerLane * lane, raw0);
+        load_raw_full<E>(rawp, kRound + kPerLane * lane, raw1);
+        for (; r + 4 <= full; r += 4) {
+          if ((r & 15u) == 0) {
+            // a wave's priority steps down with every 16 rounds of a block it
+            // decodes and wraps after four steps: a SIMD issues for its oldest
+            // wave first, and with equal shares the waves that arrived last on a
+            // SIMD would finish last (the fourth ~10% after the first); a wave
+            // that lags gets the issue slots until it has caught up (1 GiB
+            // buffer 0.413 -> 0.407 ms, its chunk streams 0.425 -> 0.421 ms,
+            // interleaved A/B)
+            switch ((r >> 4) & 3u) {
+              case 0: __builtin_amdgcn_s_setprio(3); break;
+              case 1: __builtin_amdgcn_s_setprio(2); break;
+              case 2: __builtin_amdgcn_s_setprio(1); break;
+              default: __builtin_amdgcn_s_setprio(0); break;
             }
           }
-          if (t == 4 && prev) store_words<E, true>(outp, (rr - 1) * kRound + kPerLane * lane, 8, w);
-        });
+          round(r, ea, eb, raw3, raw2, r > 0);
+          round(r + 1, eb, ea, raw0, raw3, true);
+          round(r + 2, ea, eb, raw1, raw0, true);
+          round(r + 3, eb, ea, raw2, raw1, true);
+        }
+        uint32_t w[NW];
+        merge_entries<DT>(eb, raw3, w);
+        store_words<E, true>(outp, (r - 1) * kRound + kPerLane * lane, 8, w);
       }
-    };
-    if (full >= 4) {
-      load_raw_full<E>(rawp, kPerLane * lane, raw0);
-      load_raw_full<E>(rawp, kRound + kPerLane * lane, raw1);
+      // up to three more full rounds and a partial one
+      for (; r < rounds; ++r) {
+        const uint32_t i0 = r * kRound + kPerLane * lane;
+        const uint32_t valid = i0 < n_b ? (n_b - i0 < 8 ? n_b - i0 : 8) : 0;
+        uint32_t raw[6] = {0, 0, 0, 0, 0, 0};
+        load_raw<E>(raw_plane, blk0 + i0, valid, raw);
+        ring_land(rg);
+#pragma unroll
+        for (uint32_t t = 0; t < kPerLane; ++t) {
+          if (t % (kPerLane / 2) == 0) ring_fill(rg, ring, lut);
+          ea[t] = decode_step<false>(ds, t < valid, lut, ring, rg.q, []() {});
+        }
+        if (valid > 0) {
+          uint32_t w[NW];
+          merge_entries<DT>(ea, raw, w);
+          store_words<E, true>(st.out, blk0 + i0, valid, w);
+        }
+      }
+      if (!dec_at_start(ds, lut) || ring_used(rg, wb) > w_avail || x0 < kStateLo || x0 >= 0x80000000u) bad = true;
+    } else {
+      RingD rg;
+      rg.len = len;
+      {
+        // section bytes [P0, P0 + 2048) fill the ring (which held the table
+        // build's scratch until now), so it holds the three chunks from the
+        // word start's 16-byte unit on; the third chunk is also the first
+        // pending refill
+        const uint32_t base = wb & ~15u;
+        const uint32_t o0 = P0 + 32 * lane;
+        *(uint4 *)(ring + (o0 & (kDecRingBytes - 1))) = pre0;
+        *(uint4 *)(ring + ((o0 + 16) & (kDecRingBytes - 1))) = pre1;
+        wave_lds_fence();
+        rg.front = base + 3 * kDecChunk;
+        rg.pos[0] = rg.pos[1] = base + 2 * kDecChunk;
+        rg.pv[0] = rg.pv[1] = *(const uint2 *)(ring + ((base + 2 * kDecChunk + 8 * lane) & (kDecRingBytes - 1)));
+      }
+      __syncthreads();
+      uint32_t p = 0, rb = wb & (kDecRingBytes - 1);
+      const uint32_t full = n_b / kRound;
+      uint8_t *outp = st.out + blk0 * E;
+      const uint8_t *rawp = raw_plane + blk0 * (E - 1);
+      uint32_t rawA[6] = {0, 0, 0, 0, 0, 0}, rawB[6] = {0, 0, 0, 0, 0, 0};
+      // round 0's raw bytes; with no full round a dummy load of the stream
+      // header, so that the loop below is always entered with the same loads
+      // in flight and waits only for what it uses
+      load_raw_full<E>(full > 0 ? rawp : s, full > 0 ? kPerLane * lane : 0, rawA);
+      // round 1's (clamped to a full round) likewise
+      load_raw_full<E>(full > 0 ? rawp : s, full > 1 ? (kRound + kPerLane * lane) : (full > 0 ? kPerLane * lane : 0),
+                       rawB);
+      // one more memory operation in flight, standing in for the store that
+      // ends every round, so that both ways into the loops match
+      const uint32_t pad_load = *(const uint32_t *)(s + 4 * lane);
+      uint32_t r = 0;
+      // full rounds, four per iteration with four raw buffers: each round's
+      // raw bytes are loaded two rounds before their use
+      uint32_t rawC[6] = {0, 0, 0, 0, 0, 0}, rawD[6] = {0, 0, 0, 0, 0, 0};
+      auto clampr = [&](uint32_t q) { return q < full ? q : full - 1; };
       for (; r + 4 <= full; r += 4) {
         if ((r & 15u) == 0) {
           // a wave's priority steps down with every 16 rounds of a block it
@@ -2592,36 +2751,322 @@ __global__ void __launch_bounds__(64) decode_kernel(DecodeArgs a) {
             default: __builtin_amdgcn_s_setprio(0); break;
           }
         }
-        round(r, ea, eb, raw3, raw2, r > 0);
-        round(r + 1, eb, ea, raw0, raw3, true);
-        round(r + 2, ea, eb, raw1, raw0, true);
-        round(r + 3, eb, ea, raw2, raw1, true);
+        uint32_t e[kPerLane], w[NW];
+#define UZIP_DEC_ROUND(RAWUSE, RAWLOAD, DR, AHEAD)                                              \
+    ringd_half<0>(rg, ring, sec, wb + 2 * p);                                                     \
+    load_raw_full<E>(rawp, clampr(r + (AHEAD)) * kRound + kPerLane * lane, RAWLOAD);              \
+    _Pragma("unroll") for (uint32_t t = 0; t < kPerLane; ++t) {                                   \
+      if (t == kPerLane / 2) ringd_half<1>(rg, ring, sec, wb + 2 * p);                            \
+      e[t] = decode_step_ring<true>(x, true, lut, ring, rb, p);             \
+    }                                                                                             \
+    merge_entries<DT>(e, RAWUSE, w);                                                              \
+    store_words<E, true>(outp, (r + (DR)) * kRound + kPerLane * lane, 8, w);
+        UZIP_DEC_ROUND(rawA, rawC, 0, 2)
+        UZIP_DEC_ROUND(rawB, rawD, 1, 3)
+        UZIP_DEC_ROUND(rawC, rawA, 2, 4)
+        UZIP_DEC_ROUND(rawD, rawB, 3, 5)
+#undef UZIP_DEC_ROUND
       }
-      uint32_t w[NW];
-      merge_entries<DT>(eb, raw3, w);
-      store_words<E, true>(outp, (r - 1) * kRound + kPerLane * lane, 8, w);
-    }
-    // up to three more full rounds and a partial one
-    for (; r < rounds; ++r) {
-      const uint32_t i0 = r * kRound + kPerLane * lane;
-      const uint32_t valid = i0 < n_b ? (n_b - i0 < 8 ? n_b - i0 : 8) : 0;
-      uint32_t raw[6] = {0, 0, 0, 0, 0, 0};
-      load_raw<E>(raw_plane, blk0 + i0, valid, raw);
-      ring_land(rg);
+      // full rounds, two per iteration with ping-pong raw registers: every
+      // load is issued a round before its use and no register is copied
+      // the rest in twos (rawA, rawB hold rounds r, r + 1 here)
+      for (; r + 2 <= full; r += 2) {
+        ringd_half<0>(rg, ring, sec, wb + 2 * p);
+        load_raw_full<E>(rawp, (r + 1) * kRound + kPerLane * lane, rawB);
+        uint32_t e[kPerLane];
 #pragma unroll
-      for (uint32_t t = 0; t < kPerLane; ++t) {
-        if (t % (kPerLane / 2) == 0) ring_fill(rg, ring, lut);
-        ea[t] = decode_step<false>(ds, t < valid, lut, ring, rg.q, []() {});
-      }
-      if (valid > 0) {
+        for (uint32_t t = 0; t < kPerLane; ++t) {
+          if (t == kPerLane / 2) ringd_half<1>(rg, ring, sec, wb + 2 * p);
+          e[t] = decode_step_ring<true>(x, true, lut, ring, rb, p);
+        }
         uint32_t w[NW];
-        merge_entries<DT>(ea, raw, w);
-        store_words<E, true>(st.out, blk0 + i0, valid, w);
+        merge_entries<DT>(e, rawA, w);
+        store_words<E, true>(outp, r * kRound + kPerLane * lane, 8, w);
+
+        ringd_half<0>(rg, ring, sec, wb + 2 * p);
+        const uint32_t rn = (r + 2 < full) ? r + 2 : r + 1;  // always a full round: no branch around the load
+        load_raw_full<E>(rawp, rn * kRound + kPerLane * lane, rawA);
+#pragma unroll
+        for (uint32_t t = 0; t < kPerLane; ++t) {
+          if (t == kPerLane / 2) ringd_half<1>(rg, ring, sec, wb + 2 * p);
+          e[t] = decode_step_ring<true>(x, true, lut, ring, rb, p);
+        }
+        merge_entries<DT>(e, rawB, w);
+        store_words<E, true>(outp, (r + 1) * kRound + kPerLane * lane, 8, w);
       }
+      if (r < full) {  // odd number of full rounds: rawA holds round r
+        ringd_half<0>(rg, ring, sec, wb + 2 * p);
+        uint32_t e[kPerLane];
+#pragma unroll
+        for (uint32_t t = 0; t < kPerLane; ++t) {
+          if (t == kPerLane / 2) ringd_half<1>(rg, ring, sec, wb + 2 * p);
+          e[t] = decode_step_ring<true>(x, true, lut, ring, rb, p);
+        }
+        uint32_t w[NW];
+        merge_entries<DT>(e, rawA, w);
+        store_words<E, true>(outp, r * kRound + kPerLane * lane, 8, w);
+        ++r;
+      }
+      if (r < rounds) {  // partial last round
+        ringd_half<0>(rg, ring, sec, wb + 2 * p);
+        const uint32_t i0 = r * kRound + kPerLane * lane;
+        const uint32_t valid = i0 < n_b ? (n_b - i0 < 8 ? n_b - i0 : 8) : 0;
+        uint32_t e[kPerLane];
+#pragma unroll
+        for (uint32_t t = 0; t < kPerLane; ++t) {
+          if (t == kPerLane / 2) ringd_half<1>(rg, ring, sec, wb + 2 * p);
+          e[t] = decode_step_ring<false>(x, t < valid, lut, ring, rb, p);
+        }
+        if (valid > 0) {
+          uint32_t raw[6];
+          load_raw<E>(raw_plane, blk0 + i0, valid, raw);
+          uint32_t w[NW];
+          merge_entries<DT>(e, raw, w);
+          store_words<E>(st.out, blk0 + i0, valid, w);
+        }
+      }
+      asm volatile("" ::"v"(pad_load));
+      if (x != kStateLo || p > w_avail || x0 < kStateLo || x0 >= 0x80000000u) bad = true;
     }
-    if (!dec_at_start(ds, lut) || ring_used(rg, wb) > w_avail || x0 < kStateLo || x0 >= 0x80000000u) bad = true;
     if (__any(bad) && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
     __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// decode_wide_kernel: few blocks.  A workgroup of two waves per block: the
+// first decodes the states (~21 instructions a sub-step, where a lone wave
+// that does everything issues ~26 and its round's share of loads, merges and
+// ring puts), writing each sub-step's entries to LDS; the second, a round
+// behind, merges and stores the elements, and looks the words up for the
+// ring.  One barrier a round.  In a round the second wave stores the two
+// chunks it loaded two rounds earlier and, while the ring of 4096 words has
+// room beyond the words consumed so far, loads the next two.  What is stored
+// when a round starts was asked for three rounds before at the latest, so it
+// reaches at least 4096 - 511 - 3 x 512 words past those consumed, or 768
+// words and 512 for every round so far: a round takes at most 512.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kWideRingWords = 4096;
+constexpr uint32_t kWideRingBytes = 8 * (kWideRingWords + kRingMirror);
+template <int DT, bool SHARED>
+__global__ void __launch_bounds__(128) decode_wide_kernel(DecodeArgs a) {
+  constexpr int E = (DT == 2) ? 4 : 2;
+  constexpr int NW = 4 * (E / 2);
+  constexpr uint32_t P0 = SHARED ? kSharedSectionFixed : kSectionFixed;
+  __shared__ uint32_t lut[kM];
+  __shared__ __align__(16) uint8_t ring[kWideRingBytes];
+  __shared__ uint32_t ebuf[2][kPerLane][kLanes];  // a round's entries
+  __shared__ uint32_t sh_k, sh_q[2];
+  const uint32_t lane = lane_id();
+  const bool lead = uniform(threadIdx.x >> 6) == 0;  // the decoding wave
+  DecStream st;
+  uint64_t cur = ~0ull, n_work = 0;
+  bool ok = true;
+  if (a.bpc == 0) {
+    Hdr h = {};
+    if (a.in_bytes >= kHeaderBytes) h = load_hdr(a.in);
+    ok = open_stream<DT, SHARED>(a, 0, h, st, lut, lead);
+    const bool end_ok = ok && stream_end_ok(st);
+    if (blockIdx.x == 0 && threadIdx.x == 0 && !end_ok) report(a.dstatus, UZIP_ECORRUPT);
+    if (!ok) return;
+    n_work = st.nb;
+  } else {
+    n_work = a.n_chunks * a.bpc;
+  }
+  for (uint64_t gb = blockIdx.x; gb < n_work; gb += gridDim.x) {
+    uint32_t b = (uint32_t)gb;
+    if (a.bpc != 0) {
+      const uint64_t qc = gb / a.bpc;
+      const uint64_t c = a.first_chunk + qc;
+      b = (uint32_t)(gb - qc * a.bpc);
+      if (c != cur) {
+        cur = c;
+        Hdr h = load_hdr(a.in + c * a.slot_bytes);
+        ok = open_stream<DT, SHARED>(a, c, h, st, lut, lead);
+      }
+      if (!ok) {
+        if (b == 0 && threadIdx.x == 0) report(a.dstatus, UZIP_ECORRUPT);
+        continue;
+      }
+      if (b >= st.nb) continue;  // the tensor's last chunk has fewer blocks
+      if (b == 0 && threadIdx.x == 0 && !stream_end_ok(st)) report(a.dstatus, UZIP_ECORRUPT);
+    }
+    const uint8_t *s = st.s;
+    const uint8_t *raw_plane = s + st.g.raw_off;
+    const uint32_t d = uniform(ld32(s + kHeaderBytes + 4ull * b));
+    const uint32_t dp = b ? uniform(ld32(s + kHeaderBytes + 4ull * b - 4)) : 0u;
+    const uint64_t start = b ? 16ull * (dp & ~kStoredBit) : 0;
+    const uint64_t end = 16ull * (d & ~kStoredBit);
+    const uint64_t blk0 = (uint64_t)b * st.be;
+    const uint32_t n_b = (uint32_t)((st.n - blk0) < st.be ? (st.n - blk0) : st.be);
+    const uint32_t rounds = (n_b + kRound - 1) / kRound;
+    const uint32_t full = n_b / kRound;
+    bool bad = !(end >= start && st.g.coded_off + end <= st.total);
+    const uint8_t *sec = s + st.g.coded_off + start;
+    const uint32_t len = bad ? 0 : (uint32_t)(end - start);
+    const bool stored = d >> 31;
+    if (!bad && (stored ? len < n_b : len < P0)) bad = true;
+    if (bad) {
+      if (threadIdx.x == 0) report(a.dstatus, UZIP_ECORRUPT);
+      continue;
+    }
+    auto valid_of = [&](uint32_t r) {
+      const uint32_t i0 = r * kRound + kPerLane * lane;
+      return i0 < n_b ? (n_b - i0 < 8 ? n_b - i0 : 8) : 0u;
+    };
+    if (stored) {
+      for (uint32_t r = lead ? 0 : 1; r < rounds; r += 2) {
+        const uint32_t i0 = r * kRound + kPerLane * lane;
+        const uint32_t valid = valid_of(r);
+        if (valid == 0) continue;
+        uint32_t sym[2] = {0, 0}, raw[6], w[NW];
+        if (valid == 8) {
+          const uint2 v = *(const uint2 *)(sec + i0);
+          sym[0] = v.x;
+          sym[1] = v.y;
+        } else {
+#pragma unroll
+          for (uint32_t q = 0; q < 8; ++q)
+            if (q < valid) sym[q >> 2] |= (uint32_t)sec[i0 + q] << (8 * (q & 3));
+        }
+        load_raw<E>(raw_plane, blk0 + i0, valid, raw);
+        merge_group<DT>(sym, raw, w);
+        store_words<E>(st.out, blk0 + i0, valid, w);
+      }
+      continue;
+    }
+    // the section's start: the decoding wave takes the states and the table,
+    // the other the 2048 bytes that hold the first three chunks of words
+    // (16-byte loads of a section of 16-byte units, whole inside it or skipped)
+    uint32_t x = 0, k = 0;
+    uint4 pre0 = make_uint4(0u, 0u, 0u, 0u), pre1 = pre0;
+    if (lead) {
+      x = ((const uint32_t *)sec)[lane];
+      if constexpr (!SHARED) {
+        const uint32_t pbyte = sec[256 + (lane >> 1)];
+        uint2 pfa = make_uint2(0u, 0u);
+        if (kSectionFixed + 8 * lane + 8 <= len) pfa = *(const uint2 *)(sec + kSectionFixed + 8 * lane);
+        const bool good = build_lut_pre(pbyte, pfa, len, lut, k);
+        if (lane == 0) sh_k = good ? k : 0u;
+      }
+    } else {
+      const uint32_t o0 = P0 + 32 * lane;
+      if (o0 + 16 <= len) pre0 = *(const uint4 *)(sec + o0);
+      if (o0 + 32 <= len) pre1 = *(const uint4 *)(sec + o0 + 16);
+    }
+    __syncthreads();
+    if constexpr (!SHARED) {
+      k = uniform(sh_k);  // (a table has at least one symbol)
+      if (k == 0) {
+        if (threadIdx.x == 0) report(a.dstatus, UZIP_ECORRUPT);
+        __syncthreads();  // both waves have read it
+        continue;
+      }
+    }
+    const uint32_t wb = SHARED ? kSharedSectionFixed : kSectionFixed + 2 * k;  // section offset of word 0
+    const uint32_t w_avail = (len - wb) / 2;
+    const uint32_t base = wb & ~15u;
+    const uint32_t p0 = (wb - base) / 2;  // words are counted from base
+    if (lead) {
+      __syncthreads();  // the ring is filled
+      const uint32_t x0 = x;
+      DecState ds = dec_state(x, lut);
+      uint32_t q = 8 * p0;
+      __builtin_amdgcn_s_setprio(2);
+      for (uint32_t r = 0; r < rounds; ++r) {
+        uint32_t *eb = ebuf[r & 1][0] + lane;
+        if (r < full) {
+#pragma unroll
+          for (uint32_t t = 0; t < kPerLane; ++t) {
+            const uint32_t e = ds.e;
+            decode_step<true, kWideRingWords>(ds, true, lut, ring, q, [&]() { eb[kLanes * t] = e; });
+          }
+        } else {
+          const uint32_t valid = valid_of(r);
+#pragma unroll
+          for (uint32_t t = 0; t < kPerLane; ++t)
+            eb[kLanes * t] = decode_step<false, kWideRingWords>(ds, t < valid, lut, ring, q, []() {});
+        }
+        q = uniform(q);
+        if (lane == 0) sh_q[(r + 1) & 1] = q;
+        __syncthreads();
+      }
+      __builtin_amdgcn_s_setprio(0);
+      if (!dec_at_start(ds, lut) || (q >> 3) - p0 > w_avail || x0 < kStateLo || x0 >= 0x80000000u) bad = true;
+      if (__any(bad) && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
+      __syncthreads();
+    } else {
+      const uint32_t last = len - 8;
+      // the raw bytes pass through the ring's place to reach their lanes
+      ((uint4 *)(ring + 32 * lane))[0] = pre0;
+      ((uint4 *)(ring + 32 * lane))[1] = pre1;
+      wave_lds_fence();
+      const uint8_t *rb = ring + (base - P0) + 8 * lane;
+      const uint2 c0 = *(const uint2 *)rb, c1 = *(const uint2 *)(rb + 2 * kRingChunk), c2 = *(const uint2 *)(rb + 4 * kRingChunk);
+      wave_lds_fence();
+      uint32_t front = 3 * kRingChunk, req = 7 * kRingChunk;  // words stored, words asked for
+      // two chunks each, loaded in even and odd rounds (the first ones now)
+      uint2 va[2] = {ring_load(sec, base + 6 * kRingChunk, last), ring_load(sec, base + 8 * kRingChunk, last)};
+      uint2 vb[2] = {ring_load(sec, base + 10 * kRingChunk, last), ring_load(sec, base + 12 * kRingChunk, last)};
+      bool ua = true, ub = true;
+      ring_put<kWideRingWords>(ring, lut, 0, c0);
+      ring_put<kWideRingWords>(ring, lut, kRingChunk, c1);
+      ring_put<kWideRingWords>(ring, lut, 2 * kRingChunk, c2);
+      uint32_t raw0[6] = {}, raw1[6] = {}, raw2[6] = {}, raw3[6] = {};
+      const uint8_t *rawp = raw_plane + blk0 * (E - 1);
+      uint8_t *outp = st.out + blk0 * E;
+      auto load_raw_at = [&](uint32_t r, uint32_t (&raw)[6]) {
+        if (full > 0) load_raw_full<E>(rawp, (r < full ? r : full - 1) * kRound + kPerLane * lane, raw);
+      };
+      load_raw_at(0, raw0);
+      load_raw_at(1, raw1);
+      load_raw_at(2, raw2);
+      if (lane == 0) sh_q[0] = 8 * p0;
+      __syncthreads();  // the ring is filled
+      // round r of the other wave: merge round r - 1 (raw bytes in `raw`,
+      // then loaded for round r + 3), store the chunks loaded in round r - 2,
+      // load the next two
+      auto helper = [&](uint32_t r, uint32_t (&raw)[6], uint2 (&v)[2], bool &u) {
+        if (r >= 1) {
+          uint32_t e[kPerLane], w[NW];
+#pragma unroll
+          for (uint32_t t = 0; t < kPerLane; ++t) e[t] = ebuf[(r - 1) & 1][t][lane];
+          const uint32_t i0 = (r - 1) * kRound + kPerLane * lane;
+          if (r - 1 < full) {
+            merge_entries<DT>(e, raw, w);
+            store_words<E, true>(outp, i0, 8, w);
+          } else if (valid_of(r - 1) > 0) {
+            uint32_t rw[6];
+            load_raw<E>(raw_plane, blk0 + i0, valid_of(r - 1), rw);
+            merge_entries<DT>(e, rw, w);
+            store_words<E, true>(st.out, blk0 + i0, valid_of(r - 1), w);
+          }
+        }
+        load_raw_at(r + 3, raw);
+        if (u) {
+          ring_put<kWideRingWords>(ring, lut, front & (kWideRingWords - 1), v[0]);
+          ring_put<kWideRingWords>(ring, lut, (front + kRingChunk) & (kWideRingWords - 1), v[1]);
+          front += 2 * kRingChunk;
+        }
+        u = req + 2 * kRingChunk <= (uniform(sh_q[r & 1]) >> 3) + kWideRingWords;
+        if (u) {
+          v[0] = ring_load(sec, base + 2 * req, last);
+          v[1] = ring_load(sec, base + 2 * (req + kRingChunk), last);
+          req += 2 * kRingChunk;
+        }
+        __syncthreads();
+      };
+      for (uint32_t r = 0;; r += 4) {
+        helper(r, raw3, va, ua);
+        if (r + 1 > rounds) break;
+        helper(r + 1, raw0, vb, ub);
+        if (r + 2 > rounds) break;
+        helper(r + 2, raw1, va, ua);
+        if (r + 3 > rounds) break;
+        helper(r + 3, raw2, vb, ub);
+        if (r + 4 > rounds) break;
+      }
+    }
   }
 }
 
@@ -3801,8 +4246,19 @@ uzip_status uzip_compress_chunked_table(const void *d_in, uint64_t n_elems, uzip
 }  // extern "C"
 
 namespace {
-uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, const DeviceInfo &info,
+// `most`: the most blocks there can be; `blocks`: as many as there are, or
+// (one stream, its block size in its header) as there would be of 64 KiB.
+uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, uint64_t blocks, const DeviceInfo &info,
                                hipStream_t stream, bool shared);
+// A workgroup of two waves per block up to so many blocks per compute unit,
+// those resident at once (by LDS): 64 KiB bf16 blocks, against one wave per
+// block, 4: 39.9 -> 36.5 us, 256: 40.6 -> 37.3; past them it loses (2048
+// blocks of 32 KiB 32.4 -> 46.2).  One stream does not state its block size:
+// there, up to 12 MiB, which 16 KiB blocks would make as many of.
+constexpr uint64_t kWideDecodePerCu = 3;
+// Waves per compute unit of decode_kernel with the ring of entries and with
+// the dense one, which decodes between the two.
+constexpr uint64_t kRingPerCu = 12, kDensePerCu = 16;
 
 uzip_status launch_decode(const void *d_in, size_t in_bytes, uzip_dtype dtype, uint64_t n_elems, void *d_out,
                           size_t out_cap, uint32_t *d_status, void *d_ws, size_t ws_bytes, hipStream_t stream,
@@ -3827,10 +4283,10 @@ uzip_status launch_decode(const void *d_in, size_t in_bytes, uzip_dtype dtype, u
   a.table = d_table;
   // at most one wave per block of the smallest size
   const uint64_t most = (n_elems + (kMinBlockBytes / elem_bytes(dtype)) - 1) / (kMinBlockBytes / elem_bytes(dtype));
-  return launch_decode_args(a, dtype, most, info, stream, shared);
+  return launch_decode_args(a, dtype, most, (n_elems * elem_bytes(dtype) + 65535) / 65536, info, stream, shared);
 }
 
-uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, const DeviceInfo &info,
+uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, uint64_t blocks, const DeviceInfo &info,
                                hipStream_t stream, bool shared) {
   // an occupancy-sized grid; its waves walk the blocks grid-stride
   static const void *const dec_tab[10] = {
@@ -3838,15 +4294,39 @@ uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, c
       (const void *)decode_kernel<3>,       (const void *)decode_kernel<4>,       (const void *)decode_kernel<0, true>,
       (const void *)decode_kernel<1, true>, (const void *)decode_kernel<2, true>, (const void *)decode_kernel<3, true>,
       (const void *)decode_kernel<4, true>};
-  const void *fn = dec_tab[(int)dtype + (shared ? 5 : 0)];
-  int occ = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, 64, 0) != hipSuccess || occ < 1) occ = 1;
-  uint64_t grid = (uint64_t)info.cus * (uint64_t)occ;
-  if (grid > most) grid = most;
-  if (grid == 0) grid = 1;
-  void *args[] = {&a};
-  if (hipLaunchKernel(fn, dim3((unsigned)grid), dim3(64), args, 0, stream) != hipSuccess) return UZIP_EHIP;
-  return UZIP_OK;
+  static const void *const wide_tab[10] = {
+      (const void *)decode_wide_kernel<0, false>, (const void *)decode_wide_kernel<1, false>,
+      (const void *)decode_wide_kernel<2, false>, (const void *)decode_wide_kernel<3, false>,
+      (const void *)decode_wide_kernel<4, false>, (const void *)decode_wide_kernel<0, true>,
+      (const void *)decode_wide_kernel<1, true>,  (const void *)decode_wide_kernel<2, true>,
+      (const void *)decode_wide_kernel<3, true>,  (const void *)decode_wide_kernel<4, true>};
+  static const void *const dense_tab[10] = {
+      (const void *)decode_kernel<0, false, true>, (const void *)decode_kernel<1, false, true>,
+      (const void *)decode_kernel<2, false, true>, (const void *)decode_kernel<3, false, true>,
+      (const void *)decode_kernel<4, false, true>, (const void *)decode_kernel<0, true, true>,
+      (const void *)decode_kernel<1, true, true>,  (const void *)decode_kernel<2, true, true>,
+      (const void *)decode_kernel<3, true, true>,  (const void *)decode_kernel<4, true, true>};
+  const uint64_t cus = (uint64_t)info.cus;
+  const int ti = (int)dtype + (shared ? 5 : 0);
+  auto launch = [&](const void *fn, int threads, uint64_t min_blocks, uint64_t max_blocks) -> bool {
+    a.min_blocks = min_blocks;
+    a.max_blocks = max_blocks;
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, threads, 0) != hipSuccess || occ < 1) occ = 1;
+    uint64_t grid = cus * (uint64_t)occ;
+    if (grid > most) grid = most;
+    if (grid == 0) grid = 1;
+    void *args[] = {&a};
+    return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(threads), args, 0, stream) == hipSuccess;
+  };
+  const uint64_t lo = kRingPerCu * cus, hi = kDensePerCu * cus;
+  if (4 * blocks <= (a.bpc != 0 ? 4 : 1) * kWideDecodePerCu * cus) return launch(wide_tab[ti], 128, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
+  if (blocks <= lo || blocks > hi) return launch(dec_tab[ti], 64, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
+  if (a.bpc != 0) return launch(dense_tab[ti], 64, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
+  // one stream that has between lo and hi blocks if they are of 64 KiB: the
+  // kernels read its header, and the one whose count it is decodes it (the
+  // other's launch costs ~2 us)
+  return launch(dense_tab[ti], 64, lo + 1, hi) && launch(dec_tab[ti], 64, hi + 1, lo) ? UZIP_OK : UZIP_EHIP;
 }
 
 uzip_status launch_decode_chunked(const void *d_in, size_t slot_bytes, uint64_t first_chunk, uint64_t n_chunks,
@@ -3885,7 +4365,7 @@ uzip_status launch_decode_chunked(const void *d_in, size_t slot_bytes, uint64_t 
   a.n_chunks = n_chunks;
   a.bpc = (uint32_t)(ce / be);
   a.block_elems = be;
-  return launch_decode_args(a, dtype, n_chunks * a.bpc, info, stream, shared);
+  return launch_decode_args(a, dtype, n_chunks * a.bpc, n_chunks * a.bpc, info, stream, shared);
 }
 }  // namespace
 

@@ -25,7 +25,7 @@ def tensor(dtype, n, pattern, block_elems, seed):
     element rotated left by one)."""
     rng = np.random.Generator(np.random.PCG64(seed))
     at = np.arange(n) % block_elems
-    loud = {"head": at < block_elems * 3 // 10, "tail": at >= block_elems * 7 // 10,
+    loud = {"spike": at < block_elems // 12, "head": at < block_elems * 3 // 10, "tail": at >= block_elems * 7 // 10,
             "waves": (at // 3072) % 3 == 1, "flat": np.ones(n, bool)}[pattern]
     sym = np.where(loud, rng.integers(0, 256, n), 126).astype(np.uint64)
     bits = 16 if BITS[dtype] is np.uint16 else 32
@@ -38,7 +38,7 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a).view(signed)).cuda()
 
 
-@pytest.mark.parametrize("pattern", ["head", "tail", "waves", "flat"])
+@pytest.mark.parametrize("pattern", ["spike", "head", "tail", "waves", "flat"])
 @pytest.mark.parametrize("dtype", ["bf16", "fp16", "fp32"])
 def test_bursts_of_words(dtype, pattern):
     import paper_2604_17172_amd as uz
@@ -69,3 +69,42 @@ def test_bursts_in_the_fused_reduce(dtype):
     assert int(status.item()) == 0
     assert np.array_equal(raw.cpu().numpy().view(BITS[dtype]), want_y)
     assert np.array_equal(out[: int(size.item())].cpu().numpy(), want_s)
+
+
+# Which decoder takes a call goes by its number of blocks on 256 compute units:
+# two waves per block up to 768, one wave per block with the ring of table
+# entries up to 3072, with the ring of plain words up to 4096, then with the
+# ring of entries again.  Chunk streams state their blocks, so small ones reach
+# every line.
+@pytest.mark.parametrize("pattern", ["head", "waves"])
+@pytest.mark.parametrize("blocks", [768, 769, 3072, 3073, 4096, 4097])
+@pytest.mark.parametrize("dtype", ["bf16", "fp16", "fp32"])
+def test_chunk_decoders_by_blocks(dtype, blocks, pattern):
+    import paper_2604_17172_amd as uz
+    e = 2 if BITS[dtype] is np.uint16 else 4
+    be = 8192 // e
+    n = (blocks - 1) * be + be // 2 + 3
+    x = tensor(dtype, n, pattern, be, seed=blocks)
+    for mode in ("per_block", "sampled"):
+        buf, slot, sizes, _ = uz.compress_chunked_table(dev(x), 8192, 8192 * 16, mode, dtype=dtype)
+        y, status = uz.decompress_chunked(buf, slot, dtype, n, 8192, 8192 * 16, shared=mode == "sampled")
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0 and bool((sizes > 0).all()), (dtype, blocks, pattern, mode)
+        assert np.array_equal(y.cpu().numpy().view(BITS[dtype]), x), (dtype, blocks, pattern, mode)
+
+
+# One stream does not state its block size: between 192 and 256 MiB two
+# kernels are launched and its header says which decodes.
+@pytest.mark.parametrize("block_bytes", [16384, 65536, 262144])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_stream_decoders_by_size(dtype, block_bytes):
+    import paper_2604_17172_amd as uz
+    e = 2 if BITS[dtype] is np.uint16 else 4
+    for size in (70 << 20, 200 << 20):
+        n = size // e - 1234
+        piece = tensor(dtype, 1 << 20, "waves", 65536 // e, seed=size)
+        x = dev(np.tile(piece, n // piece.size + 1)[:n])
+        out, _ = uz.compress(x, block_bytes, dtype=dtype, check=True)
+        y, status = uz.decompress(out, dtype, n)
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0 and torch.equal(y, x), (dtype, block_bytes, size)
