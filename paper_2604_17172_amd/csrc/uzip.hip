@@ -3807,6 +3807,7 @@ uzip_status device_info(DeviceInfo &out) {
     };
     for (int k = 0; k < kEncodeKernels; ++k) at0 = at0 && no_static_lds(encode_kernel_ptr(k));
     for (int k = 0; k < kSharedKernels; ++k) at0 = at0 && no_static_lds(shared_kernel_ptr(k));
+    for (int k = 0; k < kWideKernels; ++k) at0 = at0 && no_static_lds(wide_kernel_ptr(k));
     for (int k = 0; k < 3; ++k) at0 = at0 && no_static_lds(reduce_kernel_ptr(k));
     g_info[dev].enc_lds_at0 = at0;
     (void)hipFuncSetAttribute((const void *)reduce_decode_kernel<0>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);

@@ -29,6 +29,10 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a).view(np.int16 if a.itemsize == 2 else np.int32)).cuda()
 
 
+def dev_bytes(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
 def values(dtype, n, seed):
     """Ordinary values with stretches of random bits (STORED blocks) and of
     one value (a table of one symbol)."""
@@ -106,3 +110,20 @@ def test_one_wave_per_block_spills_and_stores(uz, dtype):
         low = rng.integers(0, 1 << (7 if dtype == "bf16" else 10), m)
         x[: m] = (e | low | rng.integers(0, 2, m) << 15).astype(x.dtype)
     check(uz, x, dtype, be * EB[dtype])
+
+
+# The most inputs whose decoders' tables and rings, slabs and symbols fit the
+# fused reduce's LDS in the largest blocks it takes (six and five), one fewer,
+# and one more, which the two kernels take.
+@pytest.mark.parametrize("dtype,bb,n_in", [("bf16", 131072, k) for k in (5, 6, 7)] +
+                         [("fp32", 262144, k) for k in (4, 5, 6)])
+def test_fused_reduce_lds_edge(uz, dtype, bb, n_in):
+    n = 2 * bb // EB[dtype] + 4321
+    streams = [ref.compress(W.normal_bf16(n, seed=i) if dtype == "bf16" else W.grad_fp32(n, seed=i), dtype, bb)
+               for i in range(n_in)]
+    out, size, raw, status = uz.reduce_fused([dev_bytes(s) for s in streams], dtype, n, bb)
+    torch.cuda.synchronize()
+    want_s, want_y = ref.reduce(streams, dtype, n, bb)
+    assert int(status.item()) == 0
+    assert np.array_equal(raw.cpu().numpy().view(want_y.dtype), want_y)
+    assert np.array_equal(out[: int(size.item())].cpu().numpy(), want_s)
