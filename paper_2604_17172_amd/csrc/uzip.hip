@@ -4320,7 +4320,16 @@ uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, u
     void *args[] = {&a};
     return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(threads), args, 0, stream) == hipSuccess;
   };
-  const uint64_t lo = kRingPerCu * cus, hi = kDensePerCu * cus;
+  // Past the dense ring's waves the ring of entries pays where a block has few
+  // words for its elements: 1 GiB in 64 KiB blocks, dense against entries, the
+  // single ring that was here before first: bf16 414 -> 396 us with entries,
+  // fp32 464 -> 453; e4m3fn (10.4K words a block) 441, 460 with entries, 421
+  // dense; e5m2 428, 432 and 406; 512 MiB fp16 under a stream's table 217, 220
+  // and 218 (the weaker the table, the more words).  The price is the second
+  // launch where a stream has large blocks: fp16 in 256 KiB blocks under a
+  // stream's table 263 -> 273.
+  const bool wordy = dtype >= UZIP_E4M3FN || (shared && elem_bytes(dtype) == 2);
+  const uint64_t lo = kRingPerCu * cus, hi = wordy ? 1ull << 62 : kDensePerCu * cus;
   if (4 * blocks <= (a.bpc != 0 ? 4 : 1) * kWideDecodePerCu * cus) return launch(wide_tab[ti], 128, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
   if (blocks <= lo || blocks > hi) return launch(dec_tab[ti], 64, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
   if (a.bpc != 0) return launch(dense_tab[ti], 64, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;

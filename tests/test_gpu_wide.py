@@ -127,3 +127,35 @@ def test_fused_reduce_lds_edge(uz, dtype, bb, n_in):
     assert int(status.item()) == 0
     assert np.array_equal(raw.cpu().numpy().view(want_y.dtype), want_y)
     assert np.array_equal(out[: int(size.item())].cpu().numpy(), want_s)
+
+
+# FP8 pairs and 16-bit types under a stream's table stay with the decoder's
+# ring of plain words past 4096 blocks too.
+@pytest.mark.parametrize("blocks", [3072, 3073, 4097])
+@pytest.mark.parametrize("dtype,mode", [("e4m3fn", "per_block"), ("e5m2", "sampled"), ("bf16", "sampled"),
+                                        ("fp16", "sampled")])
+def test_wordy_chunks_decode(uz, dtype, mode, blocks):
+    n = (blocks - 1) * 4096 + 1234
+    x = values(dtype, n, seed=blocks)
+    buf, slot, sizes, _ = uz.compress_chunked_table(dev(x), 8192, 8192 * 16, mode, dtype=dtype)
+    y, status = uz.decompress_chunked(buf, slot, dtype, n, 8192, 8192 * 16, shared=mode == "sampled")
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0 and bool((sizes > 0).all())
+    assert np.array_equal(y.cpu().numpy().view(x.dtype), x)
+
+
+# One stream: its header says whether the plain ring (more than 3072 blocks)
+# or the ring of entries decodes.
+@pytest.mark.parametrize("block_bytes", [16384, 65536, 1 << 20])
+@pytest.mark.parametrize("dtype,mode", [("e4m3fn", "per_block"), ("e5m2", "sampled"), ("bf16", "sampled")])
+def test_wordy_stream_decode(uz, dtype, mode, block_bytes):
+    part = values(dtype, 3 * (1 << 20) + 77, seed=21)
+    n = 140 << 20
+    x = dev(part).repeat(n // part.size + 1)[:n].contiguous()
+    s, size = uz.compress_table(x, block_bytes, mode, dtype=dtype)
+    torch.cuda.synchronize()
+    s = s[: int(size.item())]
+    y, status = uz.decompress_table(s, dtype, n) if mode == "sampled" else uz.decompress(s, dtype, n)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    assert bool((y.view(torch.int16) == x).all())
