@@ -3102,12 +3102,15 @@ struct ReduceArgs {
   uint8_t *yout;           // caller's copy of it (may be null or ybuf)
   uint32_t *hist_out;      // [n_blocks][256]
   uint32_t *dstatus;
+  uint32_t hist_reps;      // reduce_decode_kernel: sub-histograms (a power of two)
   // reduce_fused_kernel: byte offsets of its LDS regions (the decoders'
   // tables and rings, later the coding pass's staging area, start at 0)
   uint32_t lds_slabs, lds_hist, lds_syms, lds_enc, lds_shared;
 };
 
-uint32_t reduce_lds(int n_in, uint32_t E) { return n_in * (kDecLds + 2 * kRound * E) + kHistBytes; }
+constexpr uint32_t reduce_lds(int n_in, uint32_t E, uint32_t reps) {
+  return n_in * (kDecLds + 2 * kRound * E) + reps * kHistStride * 4;
+}
 
 template <int DT>
 __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_decode_kernel(ReduceArgs a) {
@@ -3142,9 +3145,9 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_decode_kernel(
     if (mode == kCoded) ds = dec_state(x0, lut);
     if (mode == kBad && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
   } else {
-    for (uint32_t i = lane; i < kHistReplicas * kHistStride; i += 64) hist[i] = 0;
+    for (uint32_t i = lane; i < a.hist_reps * kHistStride; i += 64) hist[i] = 0;
   }
-  uint32_t *h = hist + (lane & (kHistReplicas - 1)) * kHistStride;
+  uint32_t *h = hist + (lane & (a.hist_reps - 1)) * kHistStride;
   __syncthreads();
 
   for (uint32_t r = 0; r < rounds; ++r) {
@@ -3252,8 +3255,7 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_decode_kernel(
   if (!decoder && a.last) {
     for (uint32_t sy = lane; sy < 256; sy += 64) {
       uint32_t c = 0;
-#pragma unroll
-      for (uint32_t rep = 0; rep < kHistReplicas; ++rep) c += hist[rep * kHistStride + sy];
+      for (uint32_t rep = 0; rep < a.hist_reps; ++rep) c += hist[rep * kHistStride + sy];
       a.hist_out[(uint64_t)b * 256 + sy] = c;
     }
   }
@@ -3938,13 +3940,30 @@ ReduceWs reduce_ws(uint64_t n_blocks, uint32_t block_elems, uint64_t n, uint32_t
   return w;
 }
 
+// Sub-histograms of reduce_decode_kernel: eight, or four where that lets one
+// more workgroup share a compute unit (its time goes by the workgroups that
+// run at once far more than by the conflicts of the one wave that counts).
+// With eight, five 16-bit inputs need 640 bytes too much for two workgroups:
+// 480 blocks of 64 KiB bf16, 229 us with eight and 173 with four; fp16 248
+// and 188; one bf16 input, 1792 blocks, 267 (six workgroups) and 218 (eight);
+// two fp32 inputs, 1792 blocks, 267 and 234.
+constexpr uint32_t kLdsMax = 160 * 1024;
+constexpr uint32_t kLdsGranule = 1280;  // LDS is given out in units of it
+constexpr uint32_t lds_residents(uint32_t lds) { return kLdsMax / ((lds + kLdsGranule - 1) / kLdsGranule * kLdsGranule); }
+constexpr uint32_t reduce_hist_reps(int n_in, uint32_t E) {
+  return lds_residents(reduce_lds(n_in, E, kHistReplicas / 2)) > lds_residents(reduce_lds(n_in, E, kHistReplicas))
+             ? kHistReplicas / 2
+             : kHistReplicas;
+}
+static_assert(lds_residents(reduce_lds(5, 2, reduce_hist_reps(5, 2))) == 2, "five 16-bit inputs: two workgroups");
+static_assert(lds_residents(reduce_lds(1, 2, reduce_hist_reps(1, 2))) >= 7, "one 16-bit input: seven workgroups");
+
 // LDS of reduce_fused_kernel for n_in decoding waves: the decoders' tables
 // and rings (or, once they are done, the staging area of a whole block's
 // words), the slabs (then the encoder table), the histogram, the block's
 // symbols and what the workgroup shares; 0 if the block does not fit (larger
 // blocks take the decode-reduce kernel and the encoder's coding pass
 // instead).
-constexpr uint32_t kLdsMax = 160 * 1024;
 uint32_t fused_layout(int n_in, uint32_t E, uint32_t block_elems, ReduceArgs *r) {
   const uint32_t stage = (uint32_t)pad16(kStageHead + 2 * word_cap(block_elems) + kStageTail);
   const uint32_t dec = (uint32_t)n_in * kDecLds;
@@ -4569,7 +4588,8 @@ uzip_status uzip_reduce_fused(const void *const *d_in, const size_t *in_bytes, i
         return UZIP_EHIP;
       return UZIP_OK;
     }
-    const uint32_t lds = reduce_lds(r.n_in, E);
+    r.hist_reps = reduce_hist_reps(r.n_in, E);
+    const uint32_t lds = reduce_lds(r.n_in, E, r.hist_reps);
     void *args[] = {&r};
     if (hipLaunchKernel(dfn, dim3((unsigned)nb), dim3(64 * (r.n_in + 1)), args, lds, stream) != hipSuccess)
       return UZIP_EHIP;

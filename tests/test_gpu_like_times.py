@@ -1,0 +1,72 @@
+"""GPU: calls that differ little take times that differ little.
+
+Which kernel takes a call, and how many of its workgroups run at once, go by
+sizes.  Each case times a call against a neighbour that another kernel or
+another number of resident workgroups takes, in turn in one process, and
+holds the ratio of the medians to a bound that lies between what was measured
+with the rule as it is and with the rule broken (both stated at the case)."""
+import statistics
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+DT = {"bf16": (2, W.normal_bf16), "fp16": (2, W.grad_fp16), "fp32": (4, W.grad_fp32)}
+
+
+@pytest.fixture(scope="module")
+def uz():
+    import paper_2604_17172_amd as m
+    return m
+
+
+def tensor(dtype, n, seed=1):
+    """n values on the GPU: 2^20 drawn ones, repeated."""
+    e, make = DT[dtype]
+    x = make(min(n, 1 << 20), seed=seed)
+    t = torch.from_numpy(x.view(np.int16 if e == 2 else np.int32)).cuda()
+    return t.repeat(-(-n // t.numel()))[:n].contiguous()
+
+
+def medians(*calls):
+    """Median microseconds of each call, the calls in turn, after 50 ms of them."""
+    begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+
+    def us(call, k):
+        begin.record()
+        for _ in range(k):
+            call()
+        end.record()
+        torch.cuda.synchronize()
+        return begin.elapsed_time(end) / k * 1e3
+
+    k = max(2, int(1000 / us(calls[0], 3)))
+    for _ in range(25):
+        for call in calls:
+            us(call, k)
+    times = [[us(call, k) for call in calls] for _ in range(21)]
+    return [statistics.median(t) for t in zip(*times)]
+
+
+def reducer(uz, dtype, n_in, blocks):
+    n = blocks * 65536 // DT[dtype][0] - 77
+    streams = []
+    for i in range(n_in):
+        s, size = uz.compress(tensor(dtype, n, seed=i), 65536, dtype=dtype)
+        streams.append(s[: int(size.item())].clone())
+    out = torch.empty(uz.uzip_max_compressed_size(uz.dtype_code(dtype), n, 65536), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(uz.uzip_workspace_size(uz.OP_REDUCE, uz.dtype_code(dtype), n, 65536, n_in), dtype=torch.uint8,
+                     device="cuda")
+    return lambda: uz.reduce_fused(streams, dtype, n, 65536, out=out, ws=ws)
+
+
+# Five inputs against four, both of two workgroups per compute unit: 1.10
+# (bf16) and 1.12 (fp16); with one workgroup of five, 1.45.
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+def test_reduce_of_five_inputs(uz, dtype):
+    five, four = medians(reducer(uz, dtype, 5, 480), reducer(uz, dtype, 4, 480))
+    assert five < 1.27 * four, (five, four)

@@ -417,6 +417,22 @@ def test_reduce_small_blocks(uz, dtype, bb):
     assert np.array_equal(host_bits(raw, dtype), want_y)
 
 
+@pytest.mark.parametrize("dtype,n_in", [("bf16", 1), ("bf16", 5), ("fp16", 5), ("fp32", 1), ("fp32", 2), ("bf16", 6)])
+def test_reduce_past_the_fused_kernel(uz, dtype, n_in):
+    """More blocks than compute units: the decode-reduce kernel with four and
+    eight sub-histograms, then the separate coding pass."""
+    n = 300 * (4096 // EB[dtype]) + 333
+    say(f"[parity] reduce past the fused kernel dtype={dtype} n_in={n_in} n={n}")
+    xs = [special_words(dtype, n, seed=600 + i) for i in range(n_in)]
+    streams = [ref.compress(v, dtype, 4096) for v in xs]
+    out, size, raw, status = uz.reduce_fused([dev(s) for s in streams], dtype, n, 4096)
+    torch.cuda.synchronize()
+    want_s, want_y = ref.reduce(streams, dtype, n, 4096)
+    assert int(status.item()) == 0
+    assert np.array_equal(out[:int(size.item())].cpu().numpy(), want_s)
+    assert np.array_equal(host_bits(raw, dtype), want_y)
+
+
 def test_reduce_sixteen_inputs_with_stored_blocks(uz):
     n = 70_000
     say("[parity] reduce n_in=16")
