@@ -49,24 +49,33 @@ def medians(*calls):
         for call in calls:
             us(call, k)
     times = [[us(call, k) for call in calls] for _ in range(21)]
-    return [statistics.median(t) for t in zip(*times)]
+    out = [statistics.median(t) for t in zip(*times)]
+    print("medians", out, "ratio", out[0] / out[1], flush=True)
+    return out
 
 
-def reducer(uz, dtype, n_in, blocks):
-    n = blocks * 65536 // DT[dtype][0] - 77
+def reducer(uz, dtype, n_in, blocks, block=65536):
+    n = blocks * block // DT[dtype][0] - 77
     streams = []
     for i in range(n_in):
-        s, size = uz.compress(tensor(dtype, n, seed=i), 65536, dtype=dtype)
+        s, size = uz.compress(tensor(dtype, n, seed=i), block, dtype=dtype)
         streams.append(s[: int(size.item())].clone())
-    out = torch.empty(uz.uzip_max_compressed_size(uz.dtype_code(dtype), n, 65536), dtype=torch.uint8, device="cuda")
-    ws = torch.empty(uz.uzip_workspace_size(uz.OP_REDUCE, uz.dtype_code(dtype), n, 65536, n_in), dtype=torch.uint8,
+    out = torch.empty(uz.uzip_max_compressed_size(uz.dtype_code(dtype), n, block), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(uz.uzip_workspace_size(uz.OP_REDUCE, uz.dtype_code(dtype), n, block, n_in), dtype=torch.uint8,
                      device="cuda")
-    return lambda: uz.reduce_fused(streams, dtype, n, 65536, out=out, ws=ws)
+    return lambda: uz.reduce_fused(streams, dtype, n, block, out=out, ws=ws)
 
 
 # Five inputs against four, both of two workgroups per compute unit: 1.10
-# (bf16) and 1.12 (fp16); with one workgroup of five, 1.45.
+# (bf16) and 1.12 (fp16); with one workgroup of five, 1.42.
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
 def test_reduce_of_five_inputs(uz, dtype):
     five, four = medians(reducer(uz, dtype, 5, 480), reducer(uz, dtype, 4, 480))
     assert five < 1.27 * four, (five, four)
+
+
+# One input in blocks of 256 KiB (two kernels) against blocks of 128 KiB (one
+# kernel): 1.97; with each round's raw bytes asked for after its sub-steps, 2.30.
+def test_reduce_in_large_blocks(uz):
+    large, small = medians(reducer(uz, "bf16", 1, 64, 262144), reducer(uz, "bf16", 1, 128, 131072))
+    assert large < 2.13 * small, (large, small)
