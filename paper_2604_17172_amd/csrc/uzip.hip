@@ -3148,6 +3148,11 @@ __global__ void __launch_bounds__(64 * (kReduceGroup + 1)) reduce_decode_kernel(
     for (uint32_t i = lane; i < a.hist_reps * kHistStride; i += 64) hist[i] = 0;
   }
   uint32_t *h = hist + (lane & (a.hist_reps - 1)) * kHistStride;
+  // With eight inputs one SIMD holds two decoding waves and the reducing one,
+  // whose round every decoder then waits for: it issues first.  64 blocks of
+  // 256 KiB, eight inputs: fp16 599 -> 543 us, bf16 531 -> 480, fp32 269 -> 263;
+  // seven fp16 inputs 528 -> 507, three 451 either way.
+  if (!decoder) __builtin_amdgcn_s_setprio(2);
   __syncthreads();
 
   for (uint32_t r = 0; r < rounds; ++r) {
