@@ -4057,11 +4057,23 @@ uzip_status launch_encode(EncodeArgs &a, uzip_dtype dt, bool reduce, uint8_t *ws
   const uint64_t chunks = ((uint64_t)a.n_blocks + a.blocks_per_chunk - 1) / a.blocks_per_chunk;
   const uint64_t most = a.n_blocks < w.slots ? a.n_blocks : w.slots;
   const bool even = chunks >= 8 * kMaxXcd || (chunks >= kMaxXcd && chunks % kMaxXcd == 0);
-  // a workgroup per block while all of them are resident at once
-  const bool wide = small && a.n_blocks <= (uint64_t)info.cus * wide_per_cu(a.block_elems);
-  a.n_xcd = (!reduce && !wide && a.flags != nullptr && info.cus == 32 * (int)kMaxXcd && even && most >= (uint64_t)info.cus)
-                ? kMaxXcd
-                : 0;
+  const bool local =
+      !reduce && a.flags != nullptr && info.cus == 32 * (int)kMaxXcd && even && most >= (uint64_t)info.cus;
+  // A workgroup per block while all of them are resident at once, but not
+  // for large fp32 blocks that can be coded XCD by XCD, equal numbers of
+  // chunks on each, once a compute unit has two: three quarters of their bytes
+  // are raw plane, and the workgroup encoder stores a chunk's bytes
+  // write-through.  fp32, 1 MiB chunks, workgroups against one wave per block
+  // XCD by XCD: 512 blocks of 128 KiB 79.7 and 63.5 us, 320 blocks 69.9 and
+  // 59.6, 256 blocks 54.8 and 59.8; 64 KiB 512 47.9 and 43.0, 384 44.5 and 40.4,
+  // 256 34.7 and 40.1; 32 KiB 512 34.0 and 36.0.  Chunks of one 64 KiB block,
+  // 512, 48.6 and 55.9 (a write-back of the XCD's L2 for each); 171 chunks, not
+  // a multiple of 8, 48.5 and 71.3.  bf16 64 KiB 512 53.0 and 58.0.
+  const bool large_raw = elem_bytes(dt) == 4 && a.block_elems >= 16384 && a.blocks_per_chunk >= 2 &&
+                         chunks % kMaxXcd == 0;
+  const bool wide = small && a.n_blocks <= (uint64_t)info.cus * wide_per_cu(a.block_elems) &&
+                    !(local && large_raw && a.n_blocks > (uint64_t)info.cus);
+  a.n_xcd = local && !wide ? kMaxXcd : 0;
   const int kind = (a.flags != nullptr && a.n_xcd == 0 ? 2 : 0) + (small ? 1 : 0);
   const void *fn = reduce   ? reduce_kernel_ptr((int)dt)
                    : shared ? shared_kernel_ptr((int)dt * 4 + kind)

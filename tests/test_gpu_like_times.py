@@ -88,3 +88,19 @@ def test_reduce_in_large_blocks(uz):
 def test_reduce_of_eight_inputs(uz, dtype):
     eight, three = medians(reducer(uz, dtype, 8, 64, 262144), reducer(uz, dtype, 3, 64, 262144))
     assert eight < 1.27 * three, (eight, three)
+
+
+def producer(uz, dtype, blocks, block, chunk):
+    n = blocks * block // DT[dtype][0] - 77
+    x = tensor(dtype, n)
+    out, _, _, flags = uz.compress_chunked(x, block, chunk, dtype=dtype)
+    ws = torch.empty(uz.uzip_workspace_size(uz.OP_CHUNKED, uz.dtype_code(dtype), n, block, chunk), dtype=torch.uint8,
+                     device="cuda")
+    return lambda: uz.compress_chunked(x, block, chunk, dtype=dtype, flags=flags, out=out, ws=ws)
+
+
+# 512 fp32 blocks of 128 KiB in 1 MiB chunks against 576, which are always
+# coded one wave per block, XCD by XCD: 0.89; by workgroups, 1.09.
+def test_producer_of_large_fp32_blocks(uz):
+    few, more = medians(producer(uz, "fp32", 512, 131072, 1 << 20), producer(uz, "fp32", 576, 131072, 1 << 20))
+    assert few < 0.98 * more, (few, more)

@@ -95,6 +95,14 @@ def test_blocks_around_the_line(uz, dtype, blocks):
     check_chunks(uz, x, dtype, 4096, 4096 * 100)
 
 
+# fp32 chunks of two and more blocks of 64 KiB, their number a multiple of 8:
+# past one block per compute unit coded XCD by XCD, else by workgroups.
+@pytest.mark.parametrize("blocks,per_chunk", [(256, 4), (258, 4), (285, 4), (272, 2), (272, 1), (512, 16)])
+def test_large_fp32_chunks(uz, blocks, per_chunk):
+    x = values("fp32", (blocks - 1) * 16384 + 999, seed=blocks + per_chunk)
+    check_chunks(uz, x, "fp32", 65536, 65536 * per_chunk)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp16", "fp32", "e4m3fn"])
 def test_one_wave_per_block_spills_and_stores(uz, dtype):
     """Past the line in the largest blocks that keep their symbols in
