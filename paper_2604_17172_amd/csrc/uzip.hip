@@ -138,6 +138,7 @@ struct DecodeArgs {
   // one stream: this launch decodes it if it has [min_blocks, max_blocks]
   // blocks, or (min_blocks > max_blocks) if it has not those between
   uint64_t min_blocks, max_blocks;
+  uint64_t pair_blocks;  // decode_wide_kernel, one stream: two waves per block for up to so many
 };
 
 // first error wins
@@ -2436,7 +2437,6 @@ __device__ bool open_stream(const DecodeArgs &a, uint64_t c, const Hdr &hv, DecS
   if (SHARED && ok && nb > 0) {
     // one lookup table for every block of the stream
     ok = build_lut_shared(mode == 1 ? (const uint16_t *)(s + table_off) : a.table, lut, fill);
-    __syncthreads();
   }
   st.be = be;
   st.nb = ok ? nb : 0;
@@ -2451,13 +2451,13 @@ __device__ inline bool stream_end_ok(const DecStream &st) {
   return st.g.coded_off + endall == st.total;
 }
 
-// DENSE: the ring of plain words.
-template <int DT, bool SHARED = false, bool DENSE = false>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DENSE ? 4 : 1))) decode_kernel(DecodeArgs a) {
+// One wave's blocks first, first + stride, ...: its table at `lut`, its words
+// at `ring` (DENSE: plain words).
+template <int DT, bool SHARED, bool DENSE>
+__device__ __forceinline__ void decode_blocks(const DecodeArgs &a, uint32_t *lut, uint8_t *ring, uint64_t first,
+                                              uint64_t stride) {
   constexpr int E = (DT == 2) ? 4 : 2;
   constexpr int NW = 4 * (E / 2);
-  __shared__ uint32_t lut[kM];
-  __shared__ __align__(16) uint8_t ring[DENSE ? kDecRingBytes : kRingBytes];
   const uint32_t lane = lane_id();
   DecStream st;
   uint64_t cur = 0, n_work = 0;
@@ -2468,10 +2468,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DENSE ?
     if (a.in_bytes >= kHeaderBytes) h = load_hdr(a.in);
     ok = open_stream<DT, SHARED>(a, 0, h, st, lut);
     if (!ok) {
-      if (blockIdx.x == 0 && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
+      if (first == 0 && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
       return;
     }
-    if (blockIdx.x == 0 && lane == 0 && !stream_end_ok(st)) report(a.dstatus, UZIP_ECORRUPT);
+    if (first == 0 && lane == 0 && !stream_end_ok(st)) report(a.dstatus, UZIP_ECORRUPT);
     n_work = st.nb;
     // two launches share a stream whose block count the host does not know:
     // one of them takes it
@@ -2510,10 +2510,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DENSE ?
   // blocks are independent: a grid-stride walk, no ticket (one counter for
   // every wave costs more in queueing than it recovers in balance)
   Ahead nx = {};
-  if (blockIdx.x < n_work) fetch(blockIdx.x, nx);
-  for (uint64_t gb = blockIdx.x; gb < n_work; gb += gridDim.x) {
+  if (first < n_work) fetch(first, nx);
+  for (uint64_t gb = first; gb < n_work; gb += stride) {
     const Ahead here = nx;
-    if (gb + gridDim.x < n_work) fetch(gb + gridDim.x, nx);
+    if (gb + stride < n_work) fetch(gb + stride, nx);
     uint32_t b = (uint32_t)gb;
     if (a.bpc != 0) {
       const uint64_t q = gb / a.bpc;
@@ -2612,7 +2612,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DENSE ?
     if constexpr (!DENSE) {
       WordRing rg;
       ring_open(rg, ring, lut, sec, len, wb, P0, pre0, pre1);
-      __syncthreads();
+      wave_lds_fence();
       DecState ds = dec_state(x, lut);
       const uint32_t full = n_b / kRound;
       uint8_t *outp = st.out + blk0 * E;
@@ -2714,7 +2714,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DENSE ?
         rg.pos[0] = rg.pos[1] = base + 2 * kDecChunk;
         rg.pv[0] = rg.pv[1] = *(const uint2 *)(ring + ((base + 2 * kDecChunk + 8 * lane) & (kDecRingBytes - 1)));
       }
-      __syncthreads();
+      wave_lds_fence();
       uint32_t p = 0, rb = wb & (kDecRingBytes - 1);
       const uint32_t full = n_b / kRound;
       uint8_t *outp = st.out + blk0 * E;
@@ -2829,8 +2829,15 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DENSE ?
       if (x != kStateLo || p > w_avail || x0 < kStateLo || x0 >= 0x80000000u) bad = true;
     }
     if (__any(bad) && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
-    __syncthreads();
+    wave_lds_fence();
   }
+}
+
+template <int DT, bool SHARED = false, bool DENSE = false>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DENSE ? 4 : 1))) decode_kernel(DecodeArgs a) {
+  __shared__ uint32_t lut[kM];
+  __shared__ __align__(16) uint8_t ring[DENSE ? kDecRingBytes : kRingBytes];
+  decode_blocks<DT, SHARED, DENSE>(a, lut, ring, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -2845,32 +2852,67 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DENSE ?
 // when a round starts was asked for three rounds before at the latest, so it
 // reaches at least 4096 - 511 - 3 x 512 words past those consumed, or 768
 // words and 512 for every round so far: a round takes at most 512.
+//
+// The host does not know how many blocks a stream has.  One with more of them
+// than workgroups are resident at once (4 and 8 KiB blocks) is decoded one
+// wave per block by four waves of each workgroup; else two of them end at
+// once.  Under a stream's table, which each of the four waves would look up
+// for itself, with more than twice as many.  12 MiB of bf16 in
+// 4 KiB blocks 29.1 -> 16.2 us, 9 MiB in 8 KiB blocks 19.4 -> 15.9; under a
+// stream's table 12 MiB in 4 KiB blocks 21.2 -> 15.7, but fp32 6 MiB in 4 KiB
+// blocks (1536) 11.4 with two waves per block and 13.0 with one.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kWideRingWords = 4096;
 constexpr uint32_t kWideRingBytes = 8 * (kWideRingWords + kRingMirror);
+constexpr uint32_t kWideDecodeWaves = 4;
 template <int DT, bool SHARED>
-__global__ void __launch_bounds__(128) decode_wide_kernel(DecodeArgs a) {
+__global__ void __launch_bounds__(64 * kWideDecodeWaves) __attribute__((amdgpu_waves_per_eu(3)))
+decode_wide_kernel(DecodeArgs a) {
   constexpr int E = (DT == 2) ? 4 : 2;
   constexpr int NW = 4 * (E / 2);
   constexpr uint32_t P0 = SHARED ? kSharedSectionFixed : kSectionFixed;
-  __shared__ uint32_t lut[kM];
-  __shared__ __align__(16) uint8_t ring[kWideRingBytes];
-  __shared__ uint32_t ebuf[2][kPerLane][kLanes];  // a round's entries
-  __shared__ uint32_t sh_k, sh_q[2];
+  struct Pair {
+    uint32_t lut[kM];
+    uint8_t ring[kWideRingBytes];
+    uint32_t ebuf[2][kPerLane][kLanes];  // a round's entries
+    uint32_t k, q[2];
+  };
+  struct One {
+    uint32_t lut[kM];
+    uint8_t ring[kRingBytes];
+  };
+  __shared__ __align__(16) union {
+    Pair pair;
+    One one[kWideDecodeWaves];
+  } sm;
+  uint32_t *lut = sm.pair.lut;
+  uint8_t *ring = sm.pair.ring;
+  auto &ebuf = sm.pair.ebuf;
+  auto &sh_k = sm.pair.k;
+  auto &sh_q = sm.pair.q;
   const uint32_t lane = lane_id();
-  const bool lead = uniform(threadIdx.x >> 6) == 0;  // the decoding wave
+  const uint32_t wave = uniform(threadIdx.x >> 6);
+  const bool lead = wave == 0;  // the decoding wave
   DecStream st;
   uint64_t cur = ~0ull, n_work = 0;
   bool ok = true;
   if (a.bpc == 0) {
     Hdr h = {};
     if (a.in_bytes >= kHeaderBytes) h = load_hdr(a.in);
+    if (uniform(h.lo.w) > a.pair_blocks) {
+      decode_blocks<DT, SHARED, false>(a, sm.one[wave].lut, sm.one[wave].ring,
+                                       (uint64_t)blockIdx.x * kWideDecodeWaves + wave,
+                                       (uint64_t)gridDim.x * kWideDecodeWaves);
+      return;
+    }
+    if (wave > 1) return;
     ok = open_stream<DT, SHARED>(a, 0, h, st, lut, lead);
     const bool end_ok = ok && stream_end_ok(st);
     if (blockIdx.x == 0 && threadIdx.x == 0 && !end_ok) report(a.dstatus, UZIP_ECORRUPT);
     if (!ok) return;
     n_work = st.nb;
   } else {
+    if (wave > 1) return;
     n_work = a.n_chunks * a.bpc;
   }
   for (uint64_t gb = blockIdx.x; gb < n_work; gb += gridDim.x) {
@@ -4374,7 +4416,12 @@ uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, u
   // stream's table 263 -> 273.
   const bool wordy = dtype >= UZIP_E4M3FN || (shared && elem_bytes(dtype) == 2);
   const uint64_t lo = kRingPerCu * cus, hi = wordy ? 1ull << 62 : kDensePerCu * cus;
-  if (4 * blocks <= (a.bpc != 0 ? 4 : 1) * kWideDecodePerCu * cus) return launch(wide_tab[ti], 128, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
+  if (4 * blocks <= (a.bpc != 0 ? 4 : 1) * kWideDecodePerCu * cus) {
+    // four waves only where there can be more blocks than workgroups
+    const int waves = a.bpc == 0 && most > kWideDecodePerCu * cus ? (int)kWideDecodeWaves : 2;
+    a.pair_blocks = (shared ? 2 : 1) * kWideDecodePerCu * cus;
+    return launch(wide_tab[ti], 64 * waves, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
+  }
   if (blocks <= lo || blocks > hi) return launch(dec_tab[ti], 64, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
   if (a.bpc != 0) return launch(dense_tab[ti], 64, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
   // one stream that has between lo and hi blocks if they are of 64 KiB: the

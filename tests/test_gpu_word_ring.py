@@ -93,6 +93,25 @@ def test_chunk_decoders_by_blocks(dtype, blocks, pattern):
         assert np.array_equal(y.cpu().numpy().view(BITS[dtype]), x), (dtype, blocks, pattern, mode)
 
 
+# One stream of up to 12 MiB goes to the kernel of two waves per block, which
+# decodes more blocks than it has workgroups (768) one wave per block.
+@pytest.mark.parametrize("mode", ["per_block", "sampled"])
+@pytest.mark.parametrize("blocks", [767, 768, 769, 1537, 3072])
+@pytest.mark.parametrize("dtype", ["bf16", "fp32", "e4m3fn"])
+def test_stream_of_small_blocks(dtype, blocks, mode):
+    import paper_2604_17172_amd as uz
+    bits = "bf16" if dtype == "e4m3fn" else dtype
+    be = 4096 // (4 if dtype == "fp32" else 2)
+    n = (blocks - 1) * be + be // 2 + 3
+    x = tensor(bits, n, "waves", be, seed=blocks)
+    x[3 * be:5 * be] = np.random.Generator(np.random.PCG64(blocks)).integers(0, 1 << 16, 2 * be)  # STORED blocks
+    s = ref.compress(x, dtype, 4096) if mode == "per_block" else ref.compress_table(x, dtype, 4096, mode)
+    y, status = uz.decompress(dev(s), dtype, n) if mode == "per_block" else uz.decompress_table(dev(s), dtype, n)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    assert np.array_equal(y.cpu().numpy().view(BITS[bits]), x)
+
+
 # One stream does not state its block size: between 192 and 256 MiB two
 # kernels are launched and its header says which decodes.
 @pytest.mark.parametrize("block_bytes", [16384, 65536, 262144])
