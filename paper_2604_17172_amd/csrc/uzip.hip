@@ -135,9 +135,10 @@ struct DecodeArgs {
   uint64_t n_chunks;
   uint32_t bpc;
   uint32_t block_elems;
-  // one stream: this launch decodes it if it has [min_blocks, max_blocks]
-  // blocks, or (min_blocks > max_blocks) if it has not those between
-  uint64_t min_blocks, max_blocks;
+  // one stream that two launches share: decode_kernel's ring of plain words
+  // takes it if its header states [plain_min, plain_max] blocks, else the ring
+  // of entries (plain_max 0: this launch is the only one)
+  uint64_t plain_min, plain_max;
   uint64_t pair_blocks;  // decode_wide_kernel, one stream: two waves per block for up to so many
 };
 
@@ -2466,6 +2467,10 @@ __device__ __forceinline__ void decode_blocks(const DecodeArgs &a, uint32_t *lut
     // one stream
     Hdr h = {};
     if (a.in_bytes >= kHeaderBytes) h = load_hdr(a.in);
+    // (before anything else, on the header as it is: both launches see the
+    // same words, and the one that goes on checks them)
+    const uint32_t stated = uniform(h.lo.w);
+    if (a.plain_max != 0 && (stated >= a.plain_min && stated <= a.plain_max) != DENSE) return;
     ok = open_stream<DT, SHARED>(a, 0, h, st, lut);
     if (!ok) {
       if (first == 0 && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
@@ -2473,10 +2478,6 @@ __device__ __forceinline__ void decode_blocks(const DecodeArgs &a, uint32_t *lut
     }
     if (first == 0 && lane == 0 && !stream_end_ok(st)) report(a.dstatus, UZIP_ECORRUPT);
     n_work = st.nb;
-    // two launches share a stream whose block count the host does not know:
-    // one of them takes it
-    const bool ge = n_work >= a.min_blocks, le = n_work <= a.max_blocks;
-    if (!(a.min_blocks <= a.max_blocks ? ge && le : ge || le)) return;
   } else {
     // chunk streams: a header is opened when the walk reaches its chunk
     cur = ~0ull;
@@ -4395,9 +4396,7 @@ uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, u
       (const void *)decode_kernel<3, true, true>,  (const void *)decode_kernel<4, true, true>};
   const uint64_t cus = (uint64_t)info.cus;
   const int ti = (int)dtype + (shared ? 5 : 0);
-  auto launch = [&](const void *fn, int threads, uint64_t min_blocks, uint64_t max_blocks) -> bool {
-    a.min_blocks = min_blocks;
-    a.max_blocks = max_blocks;
+  auto launch = [&](const void *fn, int threads) -> bool {
     int occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, fn, threads, 0) != hipSuccess || occ < 1) occ = 1;
     uint64_t grid = cus * (uint64_t)occ;
@@ -4411,23 +4410,23 @@ uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, u
   // single ring that was here before first: bf16 414 -> 396 us with entries,
   // fp32 464 -> 453; e4m3fn (10.4K words a block) 441, 460 with entries, 421
   // dense; e5m2 428, 432 and 406; 512 MiB fp16 under a stream's table 217, 220
-  // and 218 (the weaker the table, the more words).  The price is the second
-  // launch where a stream has large blocks: fp16 in 256 KiB blocks under a
-  // stream's table 263 -> 273.
+  // and 218 (the weaker the table, the more words).
   const bool wordy = dtype >= UZIP_E4M3FN || (shared && elem_bytes(dtype) == 2);
   const uint64_t lo = kRingPerCu * cus, hi = wordy ? 1ull << 62 : kDensePerCu * cus;
   if (4 * blocks <= (a.bpc != 0 ? 4 : 1) * kWideDecodePerCu * cus) {
     // four waves only where there can be more blocks than workgroups
     const int waves = a.bpc == 0 && most > kWideDecodePerCu * cus ? (int)kWideDecodeWaves : 2;
     a.pair_blocks = (shared ? 2 : 1) * kWideDecodePerCu * cus;
-    return launch(wide_tab[ti], 64 * waves, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
+    return launch(wide_tab[ti], 64 * waves) ? UZIP_OK : UZIP_EHIP;
   }
-  if (blocks <= lo || blocks > hi) return launch(dec_tab[ti], 64, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
-  if (a.bpc != 0) return launch(dense_tab[ti], 64, 0, ~0ull) ? UZIP_OK : UZIP_EHIP;
-  // one stream that has between lo and hi blocks if they are of 64 KiB: the
-  // kernels read its header, and the one whose count it is decodes it (the
-  // other's launch costs ~2 us)
-  return launch(dense_tab[ti], 64, lo + 1, hi) && launch(dec_tab[ti], 64, hi + 1, lo) ? UZIP_OK : UZIP_EHIP;
+  if (blocks <= lo || blocks > hi) return launch(dec_tab[ti], 64) ? UZIP_OK : UZIP_EHIP;
+  if (a.bpc != 0) return launch(dense_tab[ti], 64) ? UZIP_OK : UZIP_EHIP;
+  // one stream that has between lo and hi blocks if they are of 64 KiB: its
+  // header says which of two launches decodes it (the other costs ~1 us before
+  // it, 2 to 3 after it; 10 when it built a stream's lookup table first)
+  a.plain_min = lo + 1;
+  a.plain_max = hi;
+  return launch(dense_tab[ti], 64) && launch(dec_tab[ti], 64) ? UZIP_OK : UZIP_EHIP;
 }
 
 uzip_status launch_decode_chunked(const void *d_in, size_t slot_bytes, uint64_t first_chunk, uint64_t n_chunks,

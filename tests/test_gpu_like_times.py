@@ -155,3 +155,13 @@ def chunk_receiver(uz, dtype, size, block, chunk, table="per_block"):
 def test_stream_of_small_blocks(uz, dtype):
     stream, chunk = medians(stream_receiver(uz, dtype, 12 << 20, 4096), chunk_receiver(uz, dtype, 12 << 20, 4096, 12 << 20))
     assert stream < 1.3 * chunk, (stream, chunk)
+
+
+# 800 blocks of 256 KiB under a stream's table, as a stream that two launches
+# share and as a chunk stream of one launch: 1.06; with the launch that leaves
+# it building the table's lookup first, 1.15.
+def test_stream_shared_by_two_launches(uz):
+    size = 800 * 262144
+    stream, chunk = medians(stream_receiver(uz, "fp32", size, 262144, "sampled"),
+                            chunk_receiver(uz, "fp32", size, 262144, size, "sampled"))
+    assert stream < 1.10 * chunk, (stream, chunk)
