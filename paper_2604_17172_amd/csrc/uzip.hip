@@ -135,10 +135,11 @@ struct DecodeArgs {
   uint64_t n_chunks;
   uint32_t bpc;
   uint32_t block_elems;
-  // one stream that two launches share: decode_kernel's ring of plain words
-  // takes it if its header states [plain_min, plain_max] blocks, else the ring
-  // of entries (plain_max 0: this launch is the only one)
-  uint64_t plain_min, plain_max;
+  // one stream that two launches share (plain_min 0: one launch): the ring of
+  // plain words takes it if its header states [plain_min, plain_max] blocks,
+  // or from wordy_min blocks on if it has more than 0.35 words per element,
+  // else the ring of entries
+  uint64_t plain_min, plain_max, wordy_min;
   uint64_t pair_blocks;  // decode_wide_kernel, one stream: two waves per block for up to so many
 };
 
@@ -2469,8 +2470,13 @@ __device__ __forceinline__ void decode_blocks(const DecodeArgs &a, uint32_t *lut
     if (a.in_bytes >= kHeaderBytes) h = load_hdr(a.in);
     // (before anything else, on the header as it is: both launches see the
     // same words, and the one that goes on checks them)
-    const uint32_t stated = uniform(h.lo.w);
-    if (a.plain_max != 0 && (stated >= a.plain_min && stated <= a.plain_max) != DENSE) return;
+    if (a.plain_min != 0) {
+      const uint32_t blocks = uniform(h.lo.w);
+      const uint64_t total = (uint64_t)uniform(h.hi.z) | (uint64_t)uniform(h.hi.w) << 32;
+      const bool plain = (blocks >= a.plain_min && blocks <= a.plain_max) ||
+                         (blocks >= a.wordy_min && 10 * (total - (E - 1) * a.n) > 7 * a.n);
+      if (plain != DENSE) return;
+    }
     ok = open_stream<DT, SHARED>(a, 0, h, st, lut);
     if (!ok) {
       if (first == 0 && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
@@ -4345,7 +4351,7 @@ uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, u
 // there, up to 12 MiB, which 16 KiB blocks would make as many of.
 constexpr uint64_t kWideDecodePerCu = 3;
 // Waves per compute unit of decode_kernel with the ring of entries and with
-// the dense one, which decodes between the two.
+// the ring of plain words.
 constexpr uint64_t kRingPerCu = 12, kDensePerCu = 16;
 
 uzip_status launch_decode(const void *d_in, size_t in_bytes, uzip_dtype dtype, uint64_t n_elems, void *d_out,
@@ -4405,28 +4411,63 @@ uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, u
     void *args[] = {&a};
     return hipLaunchKernel(fn, dim3((unsigned)grid), dim3(threads), args, 0, stream) == hipSuccess;
   };
-  // Past the dense ring's waves the ring of entries pays where a block has few
-  // words for its elements: 1 GiB in 64 KiB blocks, dense against entries, the
-  // single ring that was here before first: bf16 414 -> 396 us with entries,
-  // fp32 464 -> 453; e4m3fn (10.4K words a block) 441, 460 with entries, 421
-  // dense; e5m2 428, 432 and 406; 512 MiB fp16 under a stream's table 217, 220
-  // and 218 (the weaker the table, the more words).
-  const bool wordy = dtype >= UZIP_E4M3FN || (shared && elem_bytes(dtype) == 2);
-  const uint64_t lo = kRingPerCu * cus, hi = wordy ? 1ull << 62 : kDensePerCu * cus;
   if (4 * blocks <= (a.bpc != 0 ? 4 : 1) * kWideDecodePerCu * cus) {
     // four waves only where there can be more blocks than workgroups
     const int waves = a.bpc == 0 && most > kWideDecodePerCu * cus ? (int)kWideDecodeWaves : 2;
     a.pair_blocks = (shared ? 2 : 1) * kWideDecodePerCu * cus;
     return launch(wide_tab[ti], 64 * waves) ? UZIP_OK : UZIP_EHIP;
   }
-  if (blocks <= lo || blocks > hi) return launch(dec_tab[ti], 64) ? UZIP_OK : UZIP_EHIP;
-  if (a.bpc != 0) return launch(dense_tab[ti], 64) ? UZIP_OK : UZIP_EHIP;
-  // one stream that has between lo and hi blocks if they are of 64 KiB: its
-  // header says which of two launches decodes it (the other costs ~1 us before
-  // it, 2 to 3 after it; 10 when it built a stream's lookup table first)
-  a.plain_min = lo + 1;
-  a.plain_max = hi;
-  return launch(dense_tab[ti], 64) && launch(dec_tab[ti], 64) ? UZIP_OK : UZIP_EHIP;
+  // The ring of plain words (16 waves per compute unit) or the ring of entries
+  // (12, a shorter chain but a table lookup for every word), us plain against
+  // entries, 64 KiB blocks where none are stated:
+  // - between 12 and 16 blocks per compute unit, where the plain ring's waves
+  //   take all blocks at once: 3500 blocks bf16 78 and 96, fp16 79 and 104;
+  //   4096 blocks of 256 KiB bf16 386 and 448, fp16 410 and 500.  Below, fewer
+  //   waves hide less of the plain ring's chain: 2048 blocks bf16 62 and 54.
+  // - past that, where a block has many words for its elements (bf16 weights
+  //   0.16 an element, e5m2 0.21, fp16 0.31, e4m3fn 0.32, 16-bit types under
+  //   a weak table of the stream up to 0.39): 8192 blocks 205 and 220 (e5m2),
+  //   213 and 237 (e4m3fn), 204 and 215 (fp16 under a table), 208 and 223 (bf16
+  //   under one of the whole weights), against 196 and 200 for bf16, 124 and 109
+  //   at 5000 blocks.  With a table per block fp16 stays with the entries, as
+  //   bf16: 207 and 220, but 128 and 120 at 5000, 164 and 160 at 6144.
+  // - fp32 (3 raw bytes an element, 16384 elements to 64 KiB) is held by
+  //   memory from 5.5 blocks per compute unit on while the tensor fits the
+  //   256 MiB last-level cache: 1633 blocks 37.9 and 42.6, 3072 74.6 and 77.5,
+  //   128 KiB 1536 66 and 74; past it 178 and 174 (3000 of 128 KiB).
+  const bool fp32 = elem_bytes(dtype) == 4;
+  const bool wordy = dtype >= UZIP_E4M3FN || (shared && !fp32);
+  const uint64_t lo = kRingPerCu * cus, hi = kDensePerCu * cus;
+  const uint64_t plain_min = fp32 ? 11 * cus / 2 + 1 : lo + 1;
+  const uint64_t plain_max = fp32 || wordy ? ~0ull : hi;
+  if (a.bpc != 0) {
+    const bool in_cache = blocks * a.block_elems <= (256ull << 20) / 4;
+    const bool plain = blocks >= plain_min && blocks <= plain_max && (!fp32 || in_cache);
+    return launch(plain ? dense_tab[ti] : dec_tab[ti], 64) ? UZIP_OK : UZIP_EHIP;
+  }
+  // One stream's blocks are in its header: two launches where it may have
+  // those of the plain ring, and the one whose they are decodes.  The idle one
+  // costs 1 to 3 us (10 when it opened the stream first), so one launch it is
+  // below 12 blocks of 64 KiB per compute unit, although the plain ring would
+  // be the better one for 3200 fp16 blocks of 32 KiB (46 and 57) and 1633 fp32
+  // blocks of 64 KiB: with two, fp16 blocks of 64 KiB lose 58 -> 60, 400 fp32
+  // blocks of 256 KiB 90 -> 92.  Past 16 of them, a table per block: where blocks
+  // of 128 KiB to 4 MiB can be between 12 and 16 (fp32 never: 4096 of 256 KiB 483
+  // plain and 459); 1 GiB of bf16 in 64 KiB blocks pays 388 -> 391.
+  bool two = wordy ? blocks > lo : fp32 && blocks > lo && blocks <= hi;
+  for (int k = 0; k <= 6 && !wordy && !fp32; ++k) two = two || (blocks > lo << k && blocks <= hi << k);
+  if (!two) return launch(dec_tab[ti], 64) ? UZIP_OK : UZIP_EHIP;
+  a.plain_min = plain_min;
+  a.plain_max = plain_max;
+  // 256 KiB, 2048 blocks: fp16 under a table 251 and 257, e4m3fn 264 and 266,
+  // bf16 under one of the whole weights 251 and 277
+  a.wordy_min = wordy ? 5 * cus + 1 : ~0ull;
+  // the one for 64 KiB blocks (fp32: 256 KiB) comes last: the idle one costs
+  // less before the other than after it
+  const bool plain_last = wordy || (!fp32 && blocks <= hi);
+  const void *const first = plain_last ? dec_tab[ti] : dense_tab[ti];
+  const void *const last = plain_last ? dense_tab[ti] : dec_tab[ti];
+  return launch(first, 64) && launch(last, 64) ? UZIP_OK : UZIP_EHIP;
 }
 
 uzip_status launch_decode_chunked(const void *d_in, size_t slot_bytes, uint64_t first_chunk, uint64_t n_chunks,

@@ -165,3 +165,20 @@ def test_stream_shared_by_two_launches(uz):
     stream, chunk = medians(stream_receiver(uz, "fp32", size, 262144, "sampled"),
                             chunk_receiver(uz, "fp32", size, 262144, size, "sampled"))
     assert stream < 1.10 * chunk, (stream, chunk)
+
+
+# 3200 blocks of 128 KiB, between 12 and 16 per compute unit, as a stream and
+# as a chunk stream: RATIO; by the ring of entries, RATIO.
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+def test_stream_between_12_and_16_blocks_per_cu(uz, dtype):
+    size = 3200 * 131072
+    stream, chunk = medians(stream_receiver(uz, dtype, size, 131072), chunk_receiver(uz, dtype, size, 131072, size))
+    assert stream < 1.11 * chunk, (stream, chunk)
+
+
+# fp32, 1633 blocks of 64 KiB against 1400, on either side of the ring of plain
+# words' line: 1.06; both by the ring of entries, 1.175.
+def test_fp32_chunks_past_six_blocks_per_cu(uz):
+    more, fewer = medians(chunk_receiver(uz, "fp32", 1633 << 16, 65536, 4 << 20),
+                          chunk_receiver(uz, "fp32", 1400 << 16, 65536, 4 << 20))
+    assert more < 1.12 * fewer, (more, fewer)

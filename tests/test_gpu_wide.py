@@ -167,3 +167,21 @@ def test_wordy_stream_decode(uz, dtype, mode, block_bytes):
     torch.cuda.synchronize()
     assert int(status.item()) == 0
     assert bool((y.view(torch.int16) == x).all())
+
+
+# A stream under a weak table (of its first 256 KiB, another distribution's):
+# past 192 MiB and from 1281 blocks on more than 0.35 words per element, which
+# its header gives, take it to the plain ring.
+@pytest.mark.parametrize("blocks", [1280, 1281])
+def test_weak_table_stream_decode(uz, blocks):
+    bb = 262144
+    n = (blocks - 1) * (bb // 2) + 777
+    x = dev(W.normal_bf16(1 << 20, sigma=0.02, seed=3)).repeat(-(-n >> 20))[:n].contiguous()
+    x[: 1 << 17] = dev(W.normal_bf16(1 << 17, sigma=1.0, seed=4))
+    s, size = uz.compress_table(x, bb, "sampled", dtype="bf16")
+    torch.cuda.synchronize()
+    size = int(size.item())
+    assert 10 * (size - n) > 7 * n
+    y, status = uz.decompress_table(s[:size], "bf16", n)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0 and bool((y.view(torch.int16) == x).all())

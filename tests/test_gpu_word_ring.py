@@ -74,10 +74,12 @@ def test_bursts_in_the_fused_reduce(dtype):
 # Which decoder takes a call goes by its number of blocks on 256 compute units:
 # two waves per block up to 768, one wave per block with the ring of table
 # entries up to 3072, with the ring of plain words up to 4096, then with the
-# ring of entries again.  Chunk streams state their blocks, so small ones reach
+# ring of entries again; 16-bit types under a stream's table (here "sampled")
+# and FP8 stay with the plain ring past 4096, and fp32 has it from 1409 on
+# (for up to 256 MiB).  Chunk streams state their blocks, so small ones reach
 # every line.
 @pytest.mark.parametrize("pattern", ["head", "waves"])
-@pytest.mark.parametrize("blocks", [768, 769, 3072, 3073, 4096, 4097])
+@pytest.mark.parametrize("blocks", [768, 769, 1408, 1409, 3072, 3073, 4096, 4097])
 @pytest.mark.parametrize("dtype", ["bf16", "fp16", "fp32"])
 def test_chunk_decoders_by_blocks(dtype, blocks, pattern):
     import paper_2604_17172_amd as uz
@@ -112,14 +114,15 @@ def test_stream_of_small_blocks(dtype, blocks, mode):
     assert np.array_equal(y.cpu().numpy().view(BITS[bits]), x)
 
 
-# One stream does not state its block size: between 192 and 256 MiB two
+# One stream does not state its block size: where the plain ring may have its
+# blocks (192 to 256 MiB, 16-bit types also twice, four times .. as much) two
 # kernels are launched and its header says which decodes.
-@pytest.mark.parametrize("block_bytes", [16384, 65536, 262144])
-@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("block_bytes", [16384, 32768, 65536, 131072, 262144])
+@pytest.mark.parametrize("dtype", ["bf16", "fp16", "fp32"])
 def test_stream_decoders_by_size(dtype, block_bytes):
     import paper_2604_17172_amd as uz
     e = 2 if BITS[dtype] is np.uint16 else 4
-    for size in (70 << 20, 200 << 20):
+    for size in (70 << 20, 200 << 20, 300 << 20, 400 << 20):
         n = size // e - 1234
         piece = tensor(dtype, 1 << 20, "waves", 65536 // e, seed=size)
         x = dev(np.tile(piece, n // piece.size + 1)[:n])
