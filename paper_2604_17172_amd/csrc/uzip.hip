@@ -126,13 +126,13 @@ struct DecodeArgs {
   const uint16_t *table;  // the caller's table (streams of table mode 2)
   // chunk streams of the split-send producer (bpc > 0): chunk c's stream in
   // the slot at in + c slot_bytes, its elements at out + c chunk_elems E;
-  // the launch decodes chunks [first_chunk, first_chunk + n_chunks), bpc
-  // blocks of block_elems each (the tensor's last chunk: fewer).  bpc == 0:
-  // one stream of n elements at in, its block count from its header.
+  // the launch decodes n_blocks blocks of block_elems from chunk first_chunk
+  // on, bpc a chunk (the tensor's last chunk: fewer).  bpc == 0: one stream of
+  // n elements at in, its block count from its header.
   uint64_t slot_bytes;
   uint64_t chunk_elems;
   uint64_t first_chunk;
-  uint64_t n_chunks;
+  uint64_t n_blocks;
   uint32_t bpc;
   uint32_t block_elems;
   // one stream that two launches share (plain_min 0: one launch): the ring of
@@ -2456,8 +2456,8 @@ __device__ inline bool stream_end_ok(const DecStream &st) {
 // One wave's blocks first, first + stride, ...: its table at `lut`, its words
 // at `ring` (DENSE: plain words).
 template <int DT, bool SHARED, bool DENSE>
-__device__ __forceinline__ void decode_blocks(const DecodeArgs &a, uint32_t *lut, uint8_t *ring, uint64_t first,
-                                              uint64_t stride) {
+__device__ __forceinline__ void decode_blocks(const DecodeArgs &a, uint32_t *lut, uint8_t *ring, uint32_t first,
+                                              uint32_t stride) {
   constexpr int E = (DT == 2) ? 4 : 2;
   constexpr int NW = 4 * (E / 2);
   const uint32_t lane = lane_id();
@@ -2487,7 +2487,7 @@ __device__ __forceinline__ void decode_blocks(const DecodeArgs &a, uint32_t *lut
   } else {
     // chunk streams: a header is opened when the walk reaches its chunk
     cur = ~0ull;
-    n_work = a.n_chunks * a.bpc;
+    n_work = a.n_blocks;
   }
 
   // The next block's directory entries, and over chunk streams its chunk's
@@ -2534,7 +2534,6 @@ __device__ __forceinline__ void decode_blocks(const DecodeArgs &a, uint32_t *lut
         if (b == 0 && lane == 0) report(a.dstatus, UZIP_ECORRUPT);
         continue;
       }
-      if (b >= st.nb) continue;  // the tensor's last chunk has fewer blocks
       if (b == 0 && lane == 0 && !stream_end_ok(st)) report(a.dstatus, UZIP_ECORRUPT);
     }
     const uint8_t *s = st.s;
@@ -2908,8 +2907,7 @@ decode_wide_kernel(DecodeArgs a) {
     if (a.in_bytes >= kHeaderBytes) h = load_hdr(a.in);
     if (uniform(h.lo.w) > a.pair_blocks) {
       decode_blocks<DT, SHARED, false>(a, sm.one[wave].lut, sm.one[wave].ring,
-                                       (uint64_t)blockIdx.x * kWideDecodeWaves + wave,
-                                       (uint64_t)gridDim.x * kWideDecodeWaves);
+                                       blockIdx.x * kWideDecodeWaves + wave, gridDim.x * kWideDecodeWaves);
       return;
     }
     if (wave > 1) return;
@@ -2920,7 +2918,7 @@ decode_wide_kernel(DecodeArgs a) {
     n_work = st.nb;
   } else {
     if (wave > 1) return;
-    n_work = a.n_chunks * a.bpc;
+    n_work = a.n_blocks;
   }
   for (uint64_t gb = blockIdx.x; gb < n_work; gb += gridDim.x) {
     uint32_t b = (uint32_t)gb;
@@ -2937,7 +2935,6 @@ decode_wide_kernel(DecodeArgs a) {
         if (b == 0 && threadIdx.x == 0) report(a.dstatus, UZIP_ECORRUPT);
         continue;
       }
-      if (b >= st.nb) continue;  // the tensor's last chunk has fewer blocks
       if (b == 0 && threadIdx.x == 0 && !stream_end_ok(st)) report(a.dstatus, UZIP_ECORRUPT);
     }
     const uint8_t *s = st.s;
@@ -4503,10 +4500,10 @@ uzip_status launch_decode_chunked(const void *d_in, size_t slot_bytes, uint64_t 
   a.slot_bytes = slot_bytes;
   a.chunk_elems = ce;
   a.first_chunk = first_chunk;
-  a.n_chunks = n_chunks;
+  a.n_blocks = (end - first_chunk * ce + be - 1) / be;
   a.bpc = (uint32_t)(ce / be);
   a.block_elems = be;
-  return launch_decode_args(a, dtype, n_chunks * a.bpc, n_chunks * a.bpc, info, stream, shared);
+  return launch_decode_args(a, dtype, a.n_blocks, a.n_blocks, info, stream, shared);
 }
 }  // namespace
 

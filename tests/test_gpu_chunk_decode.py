@@ -71,7 +71,12 @@ def oracle_slots(streams, slot):
                                            ("fp16", 4096, 16384, 100_000),
                                            ("e4m3fn", 4096, 16384, 70_001),
                                            ("bf16", 65536, 65536, 5 * 32768),
-                                           ("bf16", 1 << 22, 1 << 22, 3 * (1 << 21) + 99)])
+                                           ("bf16", 1 << 22, 1 << 22, 3 * (1 << 21) + 99),
+                                           # one chunk of 16384 blocks' room that holds fewer (each decoder)
+                                           ("bf16", 4096, 1 << 26, 30_001),
+                                           ("bf16", 4096, 1 << 26, 1000 * 2048 + 1),
+                                           ("fp16", 4096, 1 << 26, 3500 * 2048 + 1),
+                                           ("bf16", 4096, 1 << 23, (1 << 23) + 1)])
 def test_all_chunks_in_one_launch(uz, dtype, bb, cb, n):
     say(f"[chunk-decode] dtype={dtype} n={n} block={bb} chunk={cb}")
     x = data(dtype, n, seed=61)

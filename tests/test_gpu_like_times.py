@@ -182,3 +182,11 @@ def test_fp32_chunks_past_six_blocks_per_cu(uz):
     more, fewer = medians(chunk_receiver(uz, "fp32", 1633 << 16, 65536, 4 << 20),
                           chunk_receiver(uz, "fp32", 1400 << 16, 65536, 4 << 20))
     assert more < 1.12 * fewer, (more, fewer)
+
+
+# 640 blocks in one chunk that has room for 3584, which another decoder would
+# take, against a chunk of just their size: 1.00; counted as 3584, 1.42.
+def test_small_tensor_in_a_large_chunk(uz):
+    roomy, exact = medians(chunk_receiver(uz, "bf16", 40 << 20, 65536, 224 << 20),
+                           chunk_receiver(uz, "bf16", 40 << 20, 65536, 40 << 20))
+    assert roomy < 1.14 * exact, (roomy, exact)
