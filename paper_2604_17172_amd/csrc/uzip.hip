@@ -797,7 +797,9 @@ __device__ __forceinline__ void enc_step_full(uint32_t &x, const uint4 e, uint32
 
 // One round of 8 sub-steps, backwards.  Virtual staging index pos is at LDS
 // byte rel + 2 pos; trash: this lane's trash slots (one for each sub-step,
-// 128 bytes apart).
+// 128 bytes apart).  A full round starts with pos at least kRound past the
+// index at the window's start: `row` runs 1024 bytes below the words' places
+// (the store's offset makes up for it) and must not wrap below LDS byte 0.
 template <bool FULL>
 __device__ __forceinline__ void enc_round(uint32_t &x, const uint4 (&e)[8], uint32_t valid, uint32_t &pos,
                                           uint32_t rel, __attribute__((address_space(3))) uint16_t *trash) {
@@ -1691,7 +1693,7 @@ __device__ __forceinline__ void encode_body(const EncodeArgs &a) {
     f.stored = stored;
     f.spilled = spilled != a.wcap;
     f.last = last_in_chunk;
-      if (!stored) {
+    if (!stored) {
       // header bytes right before the words: states | bitmap | f[k] (states
       // only with a stream-wide table)
       write_section_head<SHARED>(stage, f.A, x, t);
@@ -3915,7 +3917,10 @@ constexpr uint32_t kSmallStageWords = 7424;                // LDS staging window
 constexpr uint32_t kMaxSlots = 2048;                        // persistent workgroups, compress
 
 bool small_path(uint32_t block_elems) { return block_elems <= kSmallMaxElems; }
-uint32_t word_cap(uint32_t block_elems) { return block_elems / 2 + kRound + 8; }
+constexpr uint32_t word_cap(uint32_t block_elems) { return block_elems / 2 + kRound + 8; }
+// (a block is STORED once it has half as many words as elements, so a round
+// of a block whose words all fit starts with kRound words' places left)
+static_assert(word_cap(0) >= kRound, "enc_round");
 uint32_t stage_words(uint32_t block_elems) {
   const uint32_t w = word_cap(block_elems);
   return w > kSmallStageWords ? kSmallStageWords : w;

@@ -46,7 +46,11 @@ constexpr uint32_t kPackedHistStride = 132; // packed 16-bit counts, two bins pe
 constexpr uint32_t kHistBytes = kHistReplicas * kHistStride * 4;
 constexpr uint32_t kEncTableBytes = 256 * 16;
 constexpr uint32_t kLutBytes = kM * 4;
-constexpr uint32_t kStageHead = 1056;       // before the words: 256 bytes (of trash slots), then room for state/bitmap/f[256]
+// LDS bytes before the words.  While a block is coded the first 1024 are trash
+// slots; after it the section's head (states, bitmap, f[256]: at most 800)
+// ends where the words begin; a packed histogram counted meanwhile for the next
+// block may take the first 256.
+constexpr uint32_t kStageHead = 1056;
 constexpr uint32_t kStageTail = 32;         // zero bytes after the words
 
 __host__ __device__ constexpr uint64_t pad16(uint64_t x) { return (x + 15u) & ~uint64_t(15); }
