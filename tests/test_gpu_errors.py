@@ -73,9 +73,29 @@ def test_compress_marks_a_stalled_stream_invalid(uz, stall):
     assert np.array_equal(out[: int(size.item())].cpu().numpy(), want)
 
 
-# 7 chunks: every workgroup takes any chunk's blocks; 81 chunks and 321
-# blocks: on a chip of 8 XCDs each chunk is coded on one XCD
-@pytest.mark.parametrize("full_chunks", [6, 80])
+def test_one_wave_encoder_marks_a_stalled_stream_invalid(uz, stall):
+    """Past 512 blocks one wave codes a block and places it after the next
+    one's first pass; here in a compress without flags."""
+    n = 700 * 2048 + 33
+    x = W.normal_bf16(n, seed=54)
+    xt = dev(x.view(np.int16))
+    want = ref.compress(x, "bf16", 4096)
+    say(f"[errors] compress n={n} in 4 KiB blocks, block 300 held, 1000 polls")
+    stall(1000, 300)
+    out, size = uz.compress(xt, 4096, dtype="bf16")
+    torch.cuda.synchronize()
+    assert int(size.item()) == 0
+    assert struct.unpack_from("<I", out[:4].cpu().numpy().tobytes())[0] == 0
+    # the last block held: nothing waits for it, the stream is valid
+    for held in (700, NONE):
+        stall(0 if held == NONE else 1000, held)
+        out, size = uz.compress(xt, 4096, dtype="bf16", check=True)
+        assert np.array_equal(out[: int(size.item())].cpu().numpy(), want), held
+
+
+# 7 and 81 chunks (25 and 321 blocks): a workgroup per block; 161 chunks (641
+# blocks): one wave per block, on a chip of 8 XCDs each chunk on one XCD
+@pytest.mark.parametrize("full_chunks", [6, 80, 160])
 def test_chunked_producer_marks_only_the_stalled_chunk(uz, stall, full_chunks):
     bb, cb = 16384, 65536               # four blocks per chunk
     x = W.normal_bf16(full_chunks * 32768 + 5000, seed=51)

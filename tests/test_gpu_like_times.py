@@ -168,7 +168,7 @@ def test_stream_shared_by_two_launches(uz):
 
 
 # 3200 blocks of 128 KiB, between 12 and 16 per compute unit, as a stream and
-# as a chunk stream: RATIO; by the ring of entries, RATIO.
+# as a chunk stream: 1.01; by the ring of entries, 1.23 (bf16) and 1.35.
 @pytest.mark.parametrize("dtype", ["bf16", "fp16"])
 def test_stream_between_12_and_16_blocks_per_cu(uz, dtype):
     size = 3200 * 131072

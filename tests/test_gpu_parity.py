@@ -521,9 +521,11 @@ def test_reduce_rejects_mismatched_inputs(uz):
 @pytest.mark.parametrize("dtype,spread", [("bf16", 64), ("bf16", 200), ("fp16", 30)])
 def test_high_entropy_blocks_spill_staging(uz, dtype, spread):
     """Exponents spread over many values: a 64 KiB block codes to more words
-    than the encoder's LDS staging window holds (it spills to the
-    workgroup's overflow slot) while the block still stays CODED (spread 64)
-    or turns STORED part way (spread 200)."""
+    than the one-wave encoder's LDS staging window holds while the block still
+    stays CODED (spread 64) or turns STORED part way (spread 200).  These few
+    blocks take the workgroup encoder, whose window holds all of a block's
+    words; past 512 blocks they spill to the workgroup's overflow slot
+    (test_one_wave_per_block_spills_and_stores)."""
     rng = np.random.default_rng(spread)
     n = 5 * 32768 + 999
     if dtype == "bf16":
