@@ -29,7 +29,8 @@
 //                   (2048 x u32) is built in LDS, its words enter an LDS
 //                   ring with their table entries and the 64 states decode
 //                   forwards.  decode_wide_kernel: two waves per block, for
-//                   few blocks.
+//                   few blocks.  A second form of decode_kernel keeps the
+//                   plain words in its ring.
 //                   For the receiver of the split-send producer the walk
 //                   covers the blocks of a range of chunk streams at once,
 //                   opening each chunk's header when it reaches that chunk.
@@ -43,7 +44,8 @@
 //                   fit in LDS), reduce_decode_kernel does the decoding and
 //                   summing and reduce_kernel, the encoder's coding half,
 //                   runs over the reduced tensor.
-//   split-send producer  encode_kernel with write-through stores and
+//   split-send producer  encode_kernel (each chunk on one XCD, or with
+//                   write-through stores) or encode_wide_kernel, with
 //                   per-chunk completion counters.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
@@ -769,6 +771,8 @@ __device__ __forceinline__ void enc_lookup8_at(uint32_t s0, uint32_t s1, uint4 (
 // sub-step on a lone wave (112 with the count right after the compare: a
 // scalar read of a fresh mask stalls the wave), 256 KiB of bf16 49.3 -> 44.7
 // us, the 1 GiB weight buffer 538 -> 524 us, 512 MiB of KV chunks 325 -> 309.
+// The FP8 types' one-wave kernel spills 8 registers with it (none before) and
+// gains all the same: 4096 e4m3fn blocks of 64 KiB 236 -> 222 us.
 //   entry e: {reciprocal, f << 20, (M - f) | shift << 24, cum}
 template <int T>
 __device__ __forceinline__ void enc_step_full(uint32_t &x, const uint4 e, uint32_t &row,
@@ -2031,12 +2035,13 @@ __global__ void __launch_bounds__(64) reduce_kernel(EncodeArgs a) {
 // e and r of its slot w & 2047.
 // Measured (interleaved A/B against the two-read chain with a ring of plain
 // words): 171 cycles a sub-step on a lone wave, 256 KiB of bf16 53.9 -> 40.3
-// us, 214 MB of fp32 119 -> 95 us, the 1 GiB weight buffer 404 -> 390 us (3
-// waves a SIMD instead of 4: it is held by memory, 4.57 TB/s).  fp32 in
-// 64 KiB blocks is the one type that loses where its blocks fit one pass
-// (1633 blocks 41.7 -> 43.6 us; 6104 blocks 181 -> 173).  A lone wave
-// issues an instruction in ~5 cycles whatever it depends on, so what is left
-// of the chain is its ~26 instructions.
+// us, 214 MB of fp32 in 256 KiB blocks 117 -> 92 us called over and over (125
+// -> 113 on other inputs each time, as most of it then comes from memory), the
+// 1 GiB weight buffer 404 -> 390 us (3 waves a SIMD instead of 4: it is held by
+// memory, 4.57 TB/s).  Where 4 waves a SIMD or few LDS reads a word count for
+// more, the ring of plain words decodes (launch_decode_args has both sides).
+// A lone wave issues an instruction in ~5 cycles whatever it depends on, so
+// what is left of the chain is its ~26 instructions.
 //
 // 512 entries and a mirror of the first 64 (one step's reads never wrap):
 // with the 8 KB table 12.5 KB of LDS per wave.  Words enter in chunks of 256
@@ -2329,8 +2334,9 @@ __device__ uint32_t open_input_block(const uint8_t *s, uint64_t in_bytes, uint64
 // chunk.  Two slots alternate by half round.  The stored frontier then stays
 // at least 512 bytes ahead of the words a half round reads, and a store never
 // overwrites unread words.  A sub-step waits for two LDS reads, one after the
-// other: this form only pays where its 16 waves take all blocks at once and
-// 12 would not (4096 blocks of 64 KiB: 89 us against 100).
+// other, but a word costs no table lookup of its own: this form pays where its
+// 16 waves take all blocks at once and 12 would not (4096 blocks of 64 KiB: 80
+// us against 97), and with many words an element or bound by memory.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kDecRingBytes = 2048;
 constexpr uint32_t kDecChunk = 512;
@@ -2745,13 +2751,7 @@ __device__ __forceinline__ void decode_blocks(const DecodeArgs &a, uint32_t *lut
       auto clampr = [&](uint32_t q) { return q < full ? q : full - 1; };
       for (; r + 4 <= full; r += 4) {
         if ((r & 15u) == 0) {
-          // a wave's priority steps down with every 16 rounds of a block it
-          // decodes and wraps after four steps: a SIMD issues for its oldest
-          // wave first, and with equal shares the waves that arrived last on a
-          // SIMD would finish last (the fourth ~10% after the first); a wave
-          // that lags gets the issue slots until it has caught up (1 GiB
-          // buffer 0.413 -> 0.407 ms, its chunk streams 0.425 -> 0.421 ms,
-          // interleaved A/B)
+          // (the priority steps as in the other ring's loop)
           switch ((r >> 4) & 3u) {
             case 0: __builtin_amdgcn_s_setprio(3); break;
             case 1: __builtin_amdgcn_s_setprio(2); break;
@@ -2775,9 +2775,9 @@ __device__ __forceinline__ void decode_blocks(const DecodeArgs &a, uint32_t *lut
         UZIP_DEC_ROUND(rawD, rawB, 3, 5)
 #undef UZIP_DEC_ROUND
       }
-      // full rounds, two per iteration with ping-pong raw registers: every
-      // load is issued a round before its use and no register is copied
-      // the rest in twos (rawA, rawB hold rounds r, r + 1 here)
+      // two more full rounds, if left (at most once; rawA, rawB hold rounds r,
+      // r + 1 here), with ping-pong raw registers: every load is issued a round
+      // before its use and no register is copied
       for (; r + 2 <= full; r += 2) {
         ringd_half<0>(rg, ring, sec, wb + 2 * p);
         load_raw_full<E>(rawp, (r + 1) * kRound + kPerLane * lane, rawB);
@@ -4453,8 +4453,8 @@ uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, u
   }
   // One stream's blocks are in its header: two launches where it may have
   // those of the plain ring, and the one whose they are decodes.  The idle one
-  // costs 1 to 3 us (10 when it opened the stream first), so one launch it is
-  // below 12 blocks of 64 KiB per compute unit, although the plain ring would
+  // costs 1 to 3 us, 5 right behind a compress (10 when it opened the stream
+  // first), so one launch it is below 12 blocks of 64 KiB per compute unit, although the plain ring would
   // be the better one for 3200 fp16 blocks of 32 KiB (46 and 57) and 1633 fp32
   // blocks of 64 KiB: with two, fp16 blocks of 64 KiB lose 58 -> 60, 400 fp32
   // blocks of 256 KiB 90 -> 92.  Past 16 of them, a table per block: where blocks
