@@ -4451,15 +4451,16 @@ uzip_status launch_decode_args(DecodeArgs &a, uzip_dtype dtype, uint64_t most, u
     const bool plain = blocks >= plain_min && blocks <= plain_max && (!fp32 || in_cache);
     return launch(plain ? dense_tab[ti] : dec_tab[ti], 64) ? UZIP_OK : UZIP_EHIP;
   }
-  // One stream's blocks are in its header: two launches where it may have
-  // those of the plain ring, and the one whose they are decodes.  The idle one
-  // costs 1 to 3 us, 5 right behind a compress (10 when it opened the stream
-  // first), so one launch it is below 12 blocks of 64 KiB per compute unit, although the plain ring would
-  // be the better one for 3200 fp16 blocks of 32 KiB (46 and 57) and 1633 fp32
-  // blocks of 64 KiB: with two, fp16 blocks of 64 KiB lose 58 -> 60, 400 fp32
-  // blocks of 256 KiB 90 -> 92.  Past 16 of them, a table per block: where blocks
-  // of 128 KiB to 4 MiB can be between 12 and 16 (fp32 never: 4096 of 256 KiB 483
-  // plain and 459); 1 GiB of bf16 in 64 KiB blocks pays 388 -> 391.
+  // One stream's blocks are in its header: two launches where it may have those
+  // of the plain ring, and the one whose they are decodes.  The idle one costs
+  // 1 to 3 us, 5 right behind a compress (10 when it opened the stream first),
+  // so one launch it is below 12 blocks of 64 KiB per compute unit, although
+  // the plain ring would be the better one for 3200 fp16 blocks of 32 KiB (46
+  // and 57) and 1633 fp32 blocks of 64 KiB: with two, fp16 blocks of 64 KiB
+  // lose 58 -> 60, 400 fp32 blocks of 256 KiB 90 -> 92.  Past 16 of them, a
+  // table per block: where blocks of 128 KiB to 4 MiB can be between 12 and 16
+  // (fp32 never: 4096 of 256 KiB 483 plain and 459); 1 GiB of bf16 in 64 KiB
+  // blocks pays 388 -> 391.
   bool two = wordy ? blocks > lo : fp32 && blocks > lo && blocks <= hi;
   for (int k = 0; k <= 6 && !wordy && !fp32; ++k) two = two || (blocks > lo << k && blocks <= hi << k);
   if (!two) return launch(dec_tab[ti], 64) ? UZIP_OK : UZIP_EHIP;
